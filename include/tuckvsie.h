@@ -67,10 +67,14 @@ typedef TV_ENUM(tv_status_e) {
   TV_ERR_WORKSPACE = -8      /* workspace missing or too small           */
 } tv_status;
 
-/* Arithmetic of the products.  FP32: factors stored as float, products on
- * FP32 MFMA with FP32 accumulation.  BF16X3: every FP32 operand x is split
- * into bf16 hi = rn(x), lo = rn(x - hi) and a*b is formed as
- * hi*hi + hi*lo + lo*hi on BF16 MFMA with FP32 accumulation. */
+/* Arithmetic of the products.  FP32: factors stored as float, products to
+ * FP32 accuracy with FP32 accumulation, on FP32 MFMA; the GEMMs of the
+ * decompress-then-GEMM path split every FP32 operand exactly into three bf16
+ * (all 24 bits for magnitudes above 2^-110) and form the six products of
+ * weight 2^-16 and above on BF16 MFMA, summed in FP32 (non-finite operands
+ * give non-finite results, NaN where an infinity might be expected).  BF16X3:
+ * every FP32 operand x is split into bf16 hi = rn(x), lo = rn(x - hi) and a*b
+ * is formed as hi*hi + hi*lo + lo*hi on BF16 MFMA with FP32 accumulation. */
 typedef TV_ENUM(tv_precision_e) { TV_PREC_FP32 = 0, TV_PREC_BF16X3 = 1 } tv_precision;
 
 /* Flag ORed into the `basis` argument of the field entry points
@@ -103,8 +107,8 @@ typedef struct {
    * tile extent along i2 and i3, column splits, and the kernel family
    * (0: phased, 1: warp-specialised producer/consumer, 2: decompress-then-
    * GEMM, for which tile_t2 is the i3 values per slab, tile_t3 the GEMM's
-   * column blocks per wave (adjoint: row blocks) and splits its k-step
-   * (adjoint: column) split count)                                         */
+   * tile width in units of 64 columns (adjoint: stacked rows) and splits its
+   * k-step (adjoint: column) split count)                                         */
   int32_t tile_t2[2], tile_t3[2], splits[2], kernel[2];
 } tv_plan_info_t;
 
@@ -190,19 +194,18 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
  *     of i3 (0: all), modes 3 and 2 of every tensor are decompressed into
  *     the stacked operand B_k = [x_1 M_1; ...] (unscaled for the adjoint) in
  *     the workspace, then the forward runs Y^k_(1) = A_k B_k as one MFMA
- *     GEMM per component (gemm_nbw = 2 or 4 column blocks per wave; splits
- *     k-step splits; BF16X3 plans split the FP32 slab into bf16 hi/lo
+ *     GEMM per component (workgroup tiles of 64 gemm_nbw columns, gemm_nbw 2
+ *     or 4; splits k-step splits; the FP32 slab is split into bf16 parts
  *     inside the GEMM); the adjoint takes
  *     Algorithm 2's sum over voxel columns first: Z_k = Y^k_(1) B_k^* as one
- *     GEMM per slab over the slab's columns (gemm_nbw 2 or 4 blocks of 32
- *     stacked rows per wave, splits 1..64 column splits, gemm_order 0:
+ *     GEMM per slab over the slab's columns (tiles of 64 gemm_nbw stacked
+ *     rows, splits 1..64 column splits, gemm_order 0:
  *     workgroups sharing B rows adjacent, 1: sharing y columns adjacent),
  *     one FP32 partial per slab and split, then x'_j = sum conj(U1_j) Z_k
  *     with the partials summed in FP64 (Algorithms 1 and 2, Sec. III.B).
  *     row_cap on path 1: 0 (the plan's GEMM tile along the voxel rows) or
- *     8 (BF16X3 plans whose 2 n1 real rows pack into 16 blocks of 32, with
- *     gemm_nbw 2: one workgroup over all voxel rows, 8 row blocks per wave,
- *     so the slab is read once per column tile).
+ *     8 (BF16X3 plans with 128 < n1 <= 256, with gemm_nbw 2: one workgroup
+ *     over all voxel rows, so the slab is read once per column tile).
  * TV_ERR_INVALID_ARG / TV_ERR_NOT_SUPPORTED for a configuration the plan
  * cannot run; the previous configuration is then kept.  Afterwards
  * tv_workspace_bytes reflects the configuration. */

@@ -121,8 +121,7 @@ static size_t arena_layout(tv_plan_s* p, char* base) {
   carve(&p->d_apack_koff, p->apack_koff.size() * sizeof(int64_t));
   carve(&p->d_split_f, splits);
   carve(&p->d_split_a, splits);
-  carve(&p->d_apack4, h.a4.size() * sizeof(float));
-  carve(&p->d_abf, h.abf.size() * sizeof(uint4));
+  carve(&p->d_abf, (p->dtg_abfoff.empty() ? 0 : p->dtg_abfoff.back()) * sizeof(uint4));
   carve(&p->d_drow, h.drow.size() * sizeof(int32_t));
   return (off + 255) & ~(size_t)255;
 }
@@ -134,7 +133,6 @@ static void clear_device_pointers(tv_plan_s* p) {
   p->d_apack_bf = nullptr;
   p->d_apack_koff = nullptr;
   p->d_split_f = p->d_split_a = nullptr;
-  p->d_apack4 = nullptr;
   p->d_abf = nullptr;
   p->d_drow = nullptr;
   p->bound = false;
@@ -365,7 +363,7 @@ static tv_status pack_plan(tv_plan_s* p) {
   p->hp.u3t = std::move(u3t);
   p->hp.apack = std::move(apack);
   p->hp.apack_bf = std::move(apack_bf);
-  if (p->with_dtg && (st = dtg_pack(p, p->hp.meta)) != TV_OK) return st;
+  if (p->with_dtg && (st = dtg_layout(p, p->hp.meta)) != TV_OK) return st;
   p->device_bytes = arena_layout(p, nullptr);
   p->finalized = true;
   return TV_OK;
@@ -388,9 +386,15 @@ static tv_status bind_arena(tv_plan_s* p, void* arena, size_t bytes, hipStream_t
   put(p->d_apack, h.apack.data(), h.apack.size() * sizeof(float));
   put(p->d_apack_bf, h.apack_bf.data(), h.apack_bf.size() * sizeof(uint4));
   put(p->d_apack_koff, p->apack_koff.data(), p->apack_koff.size() * sizeof(int64_t));
-  put(p->d_apack4, h.a4.data(), h.a4.size() * sizeof(float));
-  put(p->d_abf, h.abf.data(), h.abf.size() * sizeof(uint4));
   put(p->d_drow, h.drow.data(), h.drow.size() * sizeof(int32_t));
+  if (e == hipSuccess && p->d_abf) {
+    const tv_status s = launch_dtg_pack(p, st);
+    if (s != TV_OK) {
+      (void)hipStreamSynchronize(st);
+      clear_device_pointers(p);
+      return s;
+    }
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     clear_device_pointers(p);
@@ -566,8 +570,7 @@ size_t grow_stage_bytes(const tv_grid& g, const int rmax[3], tv_precision precis
 constexpr int kDtgRowPad = 16;
 static void dtg_grow_setup(tv_plan_s* p) {
   if (p->grid.q > DTG_MAXQ_HOST) return;
-  const int MT = dtg_mt(p);
-  p->dtg_nbtp = (p->nbt_pack + MT - 1) / MT * MT;
+  p->dtg_nbtp = dtg_blocks(p);
   p->dtg_rpad.assign(p->grid.q, 0);
   p->dtg_rows = 0;
   p->dtg_packed = true;
@@ -979,7 +982,7 @@ tv_status tv_workspace_bytes(tv_plan p, int32_t op, int32_t nrhs, size_t* bytes)
 
 static tv_status check_call(tv_plan p, const void* in, int64_t ldin, int64_t rows_in,
                             int32_t nrhs, const void* out, int64_t ldout, int64_t rows_out,
-                            int op, const void* ws, size_t ws_bytes) {
+                            const void* ws, size_t ws_bytes, size_t need) {
   if (!p) return set_error(TV_ERR_INVALID_ARG, "plan is NULL");
   if (!p->finalized) return set_error(TV_ERR_INVALID_ARG, "plan is not finalized");
   if (!p->bound)
@@ -996,9 +999,6 @@ static tv_status check_call(tv_plan p, const void* in, int64_t ldin, int64_t row
   const size_t out_len = 8 * (size_t)(ldout * (nrhs - 1) + rows_out);
   if (ib < ob + out_len && ob < ib + in_len)
     return set_error(TV_ERR_INVALID_ARG, "input and output overlap");
-  size_t need = 0;
-  tv_status st = tv_workspace_bytes(p, op, nrhs, &need);
-  if (st != TV_OK) return st;
   if (need && (!ws || ws_bytes < need)) {
     char buf[128];
     snprintf(buf, sizeof buf, "workspace of %zu bytes needed, %zu given", need,
@@ -1014,7 +1014,10 @@ tv_status tv_matvec(tv_plan p, const void* x, int64_t ldx, int32_t nrhs, void* y
   clear_error();
   if (!p) return set_error(TV_ERR_INVALID_ARG, "plan is NULL");
   const int64_t rows = (int64_t)p->grid.q * p->grid.n1 * p->grid.n2 * p->grid.n3;
-  tv_status st = check_call(p, x, ldx, p->grid.m, nrhs, y, ldy, rows, 0, ws, ws_bytes);
+  size_t need = 0;
+  tv_status st = tv_workspace_bytes(p, 0, nrhs < 1 ? 1 : nrhs, &need);
+  if (st != TV_OK) return st;
+  st = check_call(p, x, ldx, p->grid.m, nrhs, y, ldy, rows, ws, ws_bytes, need);
   if (st != TV_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   for (int32_t c = 0; c < nrhs; ++c) {
@@ -1033,19 +1036,21 @@ tv_status tv_matvec(tv_plan p, const void* x, int64_t ldx, int32_t nrhs, void* y
   return TV_OK;
 }
 
-tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x, int64_t ldx,
-                     void* ws, size_t ws_bytes, void* stream) {
-  clear_error();
-  if (!p) return set_error(TV_ERR_INVALID_ARG, "plan is NULL");
+}  // extern "C"
+
+namespace tv {
+
+tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x, int64_t ldx,
+                      void* ws, size_t ws_bytes, size_t need, int s3, int splits,
+                      hipStream_t s) {
   const int64_t rows = (int64_t)p->grid.q * p->grid.n1 * p->grid.n2 * p->grid.n3;
-  tv_status st = check_call(p, y, ldy, rows, nrhs, x, ldx, p->grid.m, 1, ws, ws_bytes);
+  tv_status st = check_call(p, y, ldy, rows, nrhs, x, ldx, p->grid.m, ws, ws_bytes, need);
   if (st != TV_OK) return st;
-  hipStream_t s = (hipStream_t)stream;
   for (int32_t c = 0; c < nrhs; ++c) {
     const float2* yc = (const float2*)y + (int64_t)c * ldy;
     float2* xc = (float2*)x + (int64_t)c * ldx;
     if (p->use_dtg[1] && dtg_supported(p)) {
-      st = launch_dtg_adjoint(p, yc, xc, ws, s);
+      st = launch_dtg_adjoint(p, yc, xc, ws, s3, splits, s);
       if (st != TV_OK) return st;
       continue;
     }
@@ -1058,4 +1063,15 @@ tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* 
   return TV_OK;
 }
 
-}  // extern "C"
+}  // namespace tv
+
+extern "C" tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x,
+                                int64_t ldx, void* ws, size_t ws_bytes, void* stream) {
+  clear_error();
+  if (!p) return set_error(TV_ERR_INVALID_ARG, "plan is NULL");
+  size_t need = 0;
+  tv_status st = tv_workspace_bytes(p, 1, nrhs < 1 ? 1 : nrhs, &need);
+  if (st != TV_OK) return st;
+  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need, p->dtg_s3_a, p->dtg_split_a,
+                     (hipStream_t)stream);
+}

@@ -26,7 +26,7 @@ static std::string plan_key(const tv_plan_s* p, int op) {
     h *= 1099511628211ull;
   }
   char buf[256];
-  snprintf(buf, sizeof buf, "k9|%s|%dx%dx%d|q%d|m%lld|p%d|r%016llx|op%d", arch.c_str(), p->grid.n1,
+  snprintf(buf, sizeof buf, "k10|%s|%dx%dx%d|q%d|m%lld|p%d|r%016llx|op%d", arch.c_str(), p->grid.n1,
            p->grid.n2, p->grid.n3, p->grid.q, (long long)p->grid.m, (int)p->precision,
            (unsigned long long)h, op);
   for (char* c = buf; *c; ++c)
@@ -112,14 +112,13 @@ static tv_status apply_config(tv_plan_s* p, int op, const tv_launch_config& c) {
     if (!dtg_supported(p)) return set_error(TV_ERR_NOT_SUPPORTED, "plan has no GEMM operand");
     if (c.slab_i3 < 0) return set_error(TV_ERR_INVALID_ARG, "slab_i3 must be >= 0");
     const int slab = c.slab_i3 ? std::min(c.slab_i3, p->grid.n3) : p->grid.n3;
-    // row_cap: 0 (the default tile) or 8 row blocks per wave, a workgroup over
-    // all 512 voxel rows (BF16X3 plans with 2 n1 = 512, gemm_nbw 2)
+    // row_cap: 0 (the default tile) or 8, a workgroup over all voxel rows
+    // (BF16X3 plans of two row tiles, gemm_nbw 2)
     if (c.row_cap != 0 && c.row_cap != 8)
       return set_error(TV_ERR_INVALID_ARG, "the GEMM takes row_cap 0 or 8");
-    if (c.row_cap == 8 && (p->precision != TV_PREC_BF16X3 || c.gemm_nbw != 2 ||
-                           p->dtg_nbtp != 16))
+    if (c.row_cap == 8 && (c.gemm_nbw != 2 || !dtg_full_row(p)))
       return set_error(TV_ERR_NOT_SUPPORTED,
-                       "row_cap 8 needs a BF16X3 plan with 2 n1 = 512 and gemm_nbw 2");
+                       "row_cap 8 needs a BF16X3 plan with 128 < n1 <= 256 and gemm_nbw 2");
     if (op == 1) {
       if (c.gemm_nbw != 2 && c.gemm_nbw != 4)
         return set_error(TV_ERR_INVALID_ARG, "the adjoint GEMM takes gemm_nbw 2 or 4");
@@ -210,7 +209,6 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
   auto cache = read_tune_cache(cache_path);
   const tv_grid& g = p->grid;
   const int64_t rows = (int64_t)g.q * g.n1 * g.n2 * g.n3;
-  const bool bf = p->precision == TV_PREC_BF16X3;
   bool dirty = false;
   for (int o = 0; o < 2; ++o) {
     if (op != 2 && op != o) continue;
@@ -286,7 +284,7 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
                 if (tiles * eff >= 4096) break;
               }
               if (sps.empty()) sps.push_back(1);
-              const bool full_m = bf && cnbw == 2 && p->dtg_nbtp == 16;
+              const bool full_m = cnbw == 2 && dtg_full_row(p);
               for (int sp : sps)
                 for (int order : {0, 1})
                   for (int rc : {0, 8}) {
@@ -308,7 +306,7 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
             c.splits = sp;
             c.row_cap = 0;
             cands.push_back(c);
-            if (bf && nbw == 2 && p->dtg_nbtp == 16) {
+            if (nbw == 2 && dtg_full_row(p)) {
               c.row_cap = 8;
               cands.push_back(c);
               c.row_cap = 0;

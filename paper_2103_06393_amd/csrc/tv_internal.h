@@ -39,8 +39,8 @@ struct Tiling {
 struct HostPack {
   std::vector<TensorMeta> meta;
   std::vector<float2> cores, u1t, u2t, u3t;
-  std::vector<float> apack, a4;
-  std::vector<uint4> apack_bf, abf;
+  std::vector<float> apack;
+  std::vector<uint4> apack_bf;
   std::vector<int32_t> drow;
 };
 
@@ -126,12 +126,10 @@ struct tv_plan_s {
   tv::HostPack hp;                   // packed data awaiting tv_plan_bind_arena
   bool bound = false;                // device pointers point into the caller's arena
   // decompress-then-GEMM form of the forward product (large grids)
-  float* d_apack4 = nullptr;       // stacked U1 in 4-k-step groups (FP32 plans)
-  int dtg_nbtp = 0;                // 32-row blocks per k-step, padded to the GEMM tile
+  int dtg_nbtp = 0;                // 32-row blocks of the 2 n1 real rows, padded to the GEMM tile
   std::vector<int64_t> dtg_rpad;   // rows of A_k padded to 16, per component
-  std::vector<int64_t> dtg_a4off;  // float offset of component k in d_apack4
   int64_t dtg_rows = 0;            // sum of dtg_rpad
-  uint4* d_abf = nullptr;          // BF16X3 plans: stacked U1 hi/lo in 8-k-step chunks
+  uint4* d_abf = nullptr;          // stacked U1 split into bf16 planes, 8-row chunks
   int32_t* d_drow = nullptr;       // first stacked row of each tensor in A_k, [k][j]
   std::vector<int64_t> dtg_abfoff; // uint4 offset of component k in d_abf
   bool with_dtg = true;             // pack the GEMM operands (FP32 plans)
@@ -141,10 +139,10 @@ struct tv_plan_s {
   int dtg_s3_a = 1 << 30;          // i3 values per slab of B (adjoint)
   int dtg_order_a = 0;             // adjoint GEMM workgroup order (tv_launch_config)
   int dtg_split_a = 1;             // column splits of the adjoint's column GEMM
-  int dtg_nbw_a = 4;               // 32-row blocks per wave along N of that GEMM
-  int dtg_nbw = 2;                 // 32-column blocks per wave of the GEMM tile
+  int dtg_nbw_a = 4;               // that GEMM's tile holds 64 dtg_nbw_a stacked rows
+  int dtg_nbw = 2;                 // the forward GEMM's tile holds 64 dtg_nbw columns
   int dtg_split = 1;               // k-step splits of the GEMM
-  int dtg_mbw[2] = {0, 0};         // GEMM 32-row blocks per wave (0: default; 8: BF16X3 full-M tile)
+  int dtg_mbw[2] = {0, 0};         // GEMM tile along the rows (0: default; 8: BF16X3, all rows)
   int max_r[3] = {0, 0, 0};
   int nbt_pack = 0;      // 32-row blocks per stacked A row in the packed layout
   int max_r12 = 0;       // largest r1 r2
@@ -195,11 +193,15 @@ int nb_cap(const tv_plan_s* p, int op);
 // (re)build and upload the column split table of one direction
 tv_status set_split(tv_plan_s* p, int op, int S);
 // decompress-then-GEMM forward (tv_dtg.hip)
-tv_status dtg_pack(tv_plan_s* p, const std::vector<TensorMeta>& meta);
+tv_status dtg_layout(tv_plan_s* p, const std::vector<TensorMeta>& meta);
+tv_status launch_dtg_pack(const tv_plan_s* p, hipStream_t st);  // set-up: A_k from the bound U1
 bool dtg_supported(const tv_plan_s* p);
-// 32-row blocks of one decompress-then-GEMM workgroup tile (tv_dtg.hip), and
-// the most components that path takes (DTG_MAXQ there)
+// 32-row blocks of one decompress-then-GEMM workgroup tile (tv_dtg.hip), of
+// all voxel rows padded to whole tiles, whether a plan takes the tile over
+// all rows, and the most components that path takes
 int dtg_mt(const tv_plan_s* p);
+int dtg_blocks(const tv_plan_s* p);
+bool dtg_full_row(const tv_plan_s* p);
 constexpr int DTG_MAXQ_HOST = 12;
 size_t dtg_workspace_bytes(const tv_plan_s* p, int op);
 int64_t dtg_launch_tiles(const tv_plan_s* p, int s3, int nbw);  // workgroups of one GEMM launch
@@ -207,8 +209,15 @@ int64_t dtg_colgemm_tiles(const tv_plan_s* p, int nbw);  // adjoint column GEMM 
 int dtg_colgemm_splits(const tv_plan_s* p, int s3);     // its column splits as launched
 tv_status launch_dtg_forward(const tv_plan_s* p, const float2* x, float2* y, void* ws,
                              hipStream_t st);
-tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, void* ws,
-                             hipStream_t st);
+// (slabs of s3 values of i3, at least `splits` column splits each)
+tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, void* ws, int s3,
+                             int splits, hipStream_t st);
+// the slab and splits that run the adjoint within a scratch of cap bytes
+bool dtg_adjoint_within(const tv_plan_s* p, size_t cap, int* s3, int* splits);
+// tv_rmatvec after its workspace query (need bytes), with the column-GEMM
+// adjoint in slabs of s3 values of i3 and at least `splits` column splits
+tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x, int64_t ldx,
+                      void* ws, size_t ws_bytes, size_t need, int s3, int splits, hipStream_t s);
 // an upper bound of the device arena of a plan of grid g whose ranks are at
 // most rmax, without the decompress-then-GEMM operands (the arena of a
 // growable plan of g.m columns)

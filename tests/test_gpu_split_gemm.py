@@ -1,0 +1,83 @@
+"""The split-bf16 GEMM of the decompress-then-GEMM products at every row tile
+(1 to 8 blocks of 32 real rows, one to three tiles) and both column tiles,
+against the FP64 oracle, and the exactness of its operand split."""
+import numpy as np
+import pytest
+
+from oracle import matvec as om
+from tests.plans import adj_terms, assert_close, fwd_terms, random_struct, struct_to_abi
+
+pytestmark = pytest.mark.gpu
+
+
+def _plan(S, prec, nbw, splits=1):
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S), precision=prec)
+    for op in (0, 1):
+        lib.tv_plan_configure(P.handle, op, path=1, splits=splits, gemm_nbw=nbw)
+    return P
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dims,q,m,rmax,nbw", [
+    ((11, 37, 7), 3, 5, 8, 4),      # 1 block
+    ((32, 19, 14), 1, 9, 8, 2),     # 2 blocks, a whole tile
+    ((47, 8, 33), 3, 4, 12, 2),     # 3 blocks, columns one past a tile
+    ((80, 16, 16), 1, 33, 12, 4),   # 5 blocks, one column tile exactly
+    ((95, 30, 9), 2, 7, 12, 2),     # 6 blocks
+    ((109, 13, 21), 3, 3, 12, 4),   # 7 blocks
+    ((128, 43, 6), 2, 6, 12, 4),    # 8 blocks, columns one short of two tiles
+    ((205, 11, 12), 1, 5, 12, 4),   # two tiles of 7 blocks
+    ((264, 9, 29), 1, 4, 10, 2),    # three tiles of 6 blocks
+])
+def test_row_tiles_match_oracle(gpu_lib, dims, q, m, rmax, nbw, prec):
+    """FP32: every entry is a sum of rounded terms: modes 3 and 2 (at most
+    rmax FP32 sums each), one rounding per chunk of the GEMM (8 stacked rows
+    or columns) and the split's dropped products (2^-23), all relative to the
+    moduli of the terms.  BF16X3: 2^-17 per product, 1e-4 as elsewhere."""
+    import torch
+    S = random_struct(dims, q, m, rmax, 7)
+    P = _plan(S, prec, nbw)
+    chunks = max(rmax * m, dims[1] * dims[2]) / 8
+    tol = 1e-4 if prec else (2 * rmax + chunks + 8) * 2.0 ** -24
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal(m) + 1j * rng.standard_normal(m)
+    y = rng.standard_normal(S.q * S.nv) + 1j * rng.standard_normal(S.q * S.nv)
+    x, y = x.astype(np.complex64), y.astype(np.complex64)
+    got = P.matvec(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert_close(got, om.alg1(S, x)[:, 0], tol, terms=fwd_terms(S, x), what="Z x")
+    got = P.rmatvec(torch.from_numpy(y).cuda()).cpu().numpy()
+    assert_close(got, om.alg2(S, y)[:, 0], tol, terms=adj_terms(S, y), what="Z^* y")
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 60])
+def test_split_is_exact_under_scaling(gpu_lib, scale):
+    """The three bf16 parts hold all 24 bits whatever the exponent: scaling the
+    operand by a power of two scales the result by it, bit for bit."""
+    import torch
+    S = random_struct((70, 12, 9), 2, 6, 8, 5)
+    P = _plan(S, 0, 4, splits=2)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    for rows, fn in ((S.m, P.matvec), (S.q * S.nv, P.rmatvec)):
+        v = torch.randn(rows, dtype=torch.complex64, device="cuda", generator=g)
+        assert torch.equal(fn(v * scale), fn(v) * scale)
+
+
+def test_noalloc_takes_what_fp32_operands_fitted(gpu_lib):
+    """An adjoint whose slab, partials and y fit the static scratch in FP32
+    but not with y as three bf16 planes runs in lower slabs there."""
+    import torch
+    from paper_2103_06393_amd import lib
+    S = random_struct((64, 64, 40), 3, 104, 6, 9)
+    P = _plan(S, 0, 4)
+    assert lib.tv_workspace_bytes(P.handle, 1, 1) > lib.TV_STATIC_SCRATCH_BYTES
+    rows = S.q * S.nv
+    y = torch.randn(rows, dtype=torch.complex64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(4))
+    x = torch.empty(S.m, dtype=torch.complex64, device="cuda")
+    lib.tv_rmatvec_noalloc(P.handle, y.data_ptr(), rows, 1, x.data_ptr(), S.m,
+                           torch.cuda.current_stream().cuda_stream)
+    ref = P.rmatvec(y)
+    # FP32 sums of 1/8 of 64 x 40 columns in another order
+    assert float((x - ref).norm() / ref.norm()) < 320 * 2.0 ** -24
