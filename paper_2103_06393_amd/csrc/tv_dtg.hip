@@ -41,12 +41,37 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// B rows of one tensor for t3w values of i3: H3[a][i3][b] = x_j sum_c
-// G[a,b,c] U3[i3,c] in LDS, then B[a][(i2, i3)] = sum_b H3[a][i3][b] U2[i2,b]
-// with each thread on one i2 and its U2 row in registers (R2MAX >= r2).
-template <int R2MAX>
-__global__ __launch_bounds__(256) void dtg_decomp_kernel(DecompParams P) {
-  extern __shared__ float2 h3[];
+// B rows of one tensor for cnt <= t3w values of i3, two small products:
+//   mode 3 (VALU):  H[p][b] = x_j sum_c G[a,b,c] U3[i3,c], p = i3l r1 + a
+//   mode 2 (v_mfma_f32_32x32x2f32):  B[p][i2] = sum_b H[p][b] U2[i2,b]
+// H sits in LDS as its Re and Im planes (row stride = 4 mod 8 floats: the
+// 16-byte reads of four b by 32 rows are free of bank conflicts); K is (b,
+// Re/Im) and the complex product's signs are in the U2 operands, which a wave
+// holds in registers for its 32 columns i2 (ure: Ur, -Ui; uim: Ui, Ur for the
+// two k), so rows of every i3 share them and one H operand feeds both parts.
+// The waves share the (column block, row block) tiles, column block first.
+// 16 i3 per workgroup fill the row blocks (8 i3 take 15% longer at 256^3) and
+// 32 KB of LDS keep four workgroups on a CU.  Write-bound where ranks are
+// small: 256^3 x 512 columns, 6.8 GB in 1.32 ms (5.2 TB/s; a fill reaches
+// 6.9), 1.75 ms with mode 2 on the VALU; 205 x 109 x 270 x 287, ranks 15 to
+// 18, 3.4 GB in 1.31 ms, where that kernel, whose threads were one i2 each,
+// took 4.0; 64^3 x 256 58 us, from 110.
+constexpr int DEC_T = 256;
+// floats per H row: b padded to fours, 4 mod 8
+__host__ __device__ inline int dec_rb(int r2) {
+  const int p = (r2 + 3) & ~3;
+  return (p & 7) ? p : p + 4;
+}
+__host__ __device__ inline int dec_rows(int r1, int t3w) { return (r1 * t3w + 31) & ~31; }
+// LDS: H planes, then {column offset, row offset} of every row p
+inline size_t dec_lds(int r1, int r2, int t3w) {
+  const size_t rows = dec_rows(r1, t3w);
+  return rows * (2 * sizeof(float) * dec_rb(r2) + sizeof(int2));
+}
+
+template <int NG>  // groups of four b, 4 NG >= r2 of every tensor
+__global__ __launch_bounds__(DEC_T) void dtg_decomp_kernel(DecompParams P) {
+  extern __shared__ v4f dsm[];
   const int64_t item = blockIdx.x;
   if (item >= P.nitems) return;
   const int64_t kt = item / P.nsub;           // k * m + j
@@ -55,94 +80,117 @@ __global__ __launch_bounds__(256) void dtg_decomp_kernel(DecompParams P) {
   const int64_t j = kt - (int64_t)k * P.m;
   const TensorMeta t = P.meta[kt];
   const int r1 = t.r1, r2 = t.r2, r3 = t.r3;
-  const int T3 = P.t3w;
-  const int i3a = P.i30 + sub * T3;
-  const int cnt = min(T3, P.i30 + P.s3 - i3a);
+  const int i3a = P.i30 + sub * P.t3w;
+  const int cnt = min(P.t3w, P.i30 + P.s3 - i3a);
+  const int np = r1 * cnt, nrow = dec_rows(r1, cnt), rb = dec_rb(r2);
+  float* Hs = reinterpret_cast<float*>(dsm);          // [part][p][b]
+  int2* tab = reinterpret_cast<int2*>(Hs + (size_t)2 * nrow * rb);
   const float2 xj = P.x ? P.x[j] : make_float2(1.f, 0.f);
   const float2* G = P.cores + t.g_off;
-  const float2* U3 = P.u3t + t.u3_off;
-  const int nh = r1 * cnt * r2;
-  for (int e = threadIdx.x; e < nh; e += 256) {
-    const int b = e % r2;
-    const int rest = e / r2;
-    const int i3l = rest % cnt;
-    const int a = rest / cnt;
-    float2 s = make_float2(0.f, 0.f);
-    const float2* g = G + a + (int64_t)r1 * b;
-    const float2* u = U3 + (int64_t)(i3a + i3l) * r3;
-    for (int c = 0; c < r3; ++c) {
-      const float2 gv = g[(int64_t)r1 * r2 * c], uv = u[c];
-      s.x = fmaf(gv.x, uv.x, fmaf(-gv.y, uv.y, s.x));
-      s.y = fmaf(gv.x, uv.y, fmaf(gv.y, uv.x, s.y));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r12 = r1 * r2;
+  // the waves' first U2 operands are in flight during mode 3
+  const int h = lane >> 5, ln = lane & 31;
+  const int npb = nrow >> 5, ntask = ((P.n2 + 31) >> 5) * npb;
+  const int task0 = ntask * wave / 4, task1 = ntask * (wave + 1) / 4;
+  float ure[4 * NG], uim[4 * NG];
+  const auto load_u2 = [&](int i2) {
+    const float2* u2 = P.u2t + t.u2_off + (int64_t)min(i2, P.n2 - 1) * r2;
+#pragma unroll
+    for (int b = 0; b < 4 * NG; ++b) {
+      const float2 u = b < r2 ? u2[b] : make_float2(0.f, 0.f);
+      ure[b] = h ? -u.y : u.x;
+      uim[b] = h ? u.x : u.y;
     }
-    h3[(a * T3 + i3l) * r2 + b] = cmul(xj, s);
+  };
+  int cb = task0 / npb, i2 = 32 * cb + ln;
+  load_u2(i2);
+  // a lane per (a, b) and 8 i3 per wave: the core fibre is read once for them,
+  // coalesced over a; U3's rows are uniform (scalar loads, constant for the
+  // kernel's lifetime)
+  typedef const __attribute__((address_space(4))) float CF;
+  CF* U3 = reinterpret_cast<CF*>(reinterpret_cast<uintptr_t>(P.u3t + t.u3_off + (int64_t)i3a * r3));
+  const int ni = (cnt + 7) >> 3;
+  for (int task = wave; task < ni * ((r12 + 63) >> 6); task += 4) {
+    const int i0 = 8 * (task % ni), ab = 64 * (task / ni) + lane;
+    if (ab >= r12) continue;
+    const int b = ab / r1, a = ab - b * r1;
+    const float2* g = G + ab;
+    float2 s[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = make_float2(0.f, 0.f);
+#pragma unroll 4
+    for (int c = 0; c < r3; ++c) {
+      const float2 gv = g[(int64_t)r12 * c];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        CF* u = U3 + 2 * (min(i0 + i, cnt - 1) * r3 + c);
+        const float ux = u[0], uy = u[1];
+        s[i].x = fmaf(gv.x, ux, fmaf(-gv.y, uy, s[i].x));
+        s[i].y = fmaf(gv.x, uy, fmaf(gv.y, ux, s[i].y));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i0 + i >= cnt) break;
+      const float2 v = cmul(xj, s[i]);
+      float* d = Hs + ((i0 + i) * r1 + a) * rb + b;
+      d[0] = v.x;
+      d[(size_t)nrow * rb] = v.y;
+    }
+  }
+  // zeros up to the next group of four b (0 times whatever LDS held could be NaN)
+  const int r2p = (r2 + 3) & ~3;
+  for (int e = tid; e < np * (r2p - r2); e += DEC_T) {
+    const int p = e % np, b = r2 + e / np;
+    Hs[p * rb + b] = 0.f;
+    Hs[(size_t)(nrow + p) * rb + b] = 0.f;
+  }
+  for (int p = tid; p < np; p += DEC_T) {
+    const int i3l = p / r1;
+    tab[p] = make_int2((i3a - P.i30 + i3l) * P.n2, (p - i3l * r1) << P.lw);
   }
   __syncthreads();
+
   float2* Bk = P.B + P.boff[k] + ((int64_t)P.drow[kt] << P.lw);
-  const int64_t bblk = (int64_t)P.rpad[k] << P.lw;  // one block of columns
+  const uint64_t bblk = (uint64_t)P.rpad[k] << P.lw;  // one block of columns
   const int nmask = (1 << P.lw) - 1;
-  // B is written once and read back by the GEMM after this kernel, and is far
-  // larger than L2 and the MALL: non-temporal stores.  With n2 even (and U2
-  // rows that fit the registers twice) each thread takes two adjacent i2,
-  // whose entries are adjacent (n even), and stores each pair as one 16-byte
-  // store; the threads' second index then strides over i3.
-  if (R2MAX <= 32 && (P.n2 & 1) == 0) {
-    const int np2 = P.n2 >> 1;
-    const int li3 = max(1, 256 / np2);
-    for (int e = threadIdx.x; e < np2 * li3; e += 256) {
-      const int i2 = 2 * (e % np2), i3s = e / np2;
-      float2 u0[R2MAX], u1[R2MAX];
-      const float2* u2 = P.u2t + t.u2_off + (int64_t)i2 * r2;
+  for (int task = task0; task < task1; ++task) {
+    const int c = task / npb, pb = task - c * npb;
+    if (c != cb) {
+      cb = c;
+      i2 = 32 * cb + ln;
+      load_u2(i2);
+    }
+    const float* hp = Hs + (size_t)(h * nrow + 32 * pb + ln) * rb;
+    v16f re = v16f{0.f}, im = v16f{0.f};
 #pragma unroll
-      for (int b = 0; b < R2MAX; ++b) {
-        u0[b] = b < r2 ? u2[b] : make_float2(0.f, 0.f);
-        u1[b] = b < r2 ? u2[r2 + b] : make_float2(0.f, 0.f);
-      }
-      for (int a = 0; a < r1; ++a) {
-        float2* row = Bk + ((int64_t)a << P.lw);
-        for (int i3l = i3s; i3l < cnt; i3l += li3) {
-          const float2* hv = h3 + (a * T3 + i3l) * r2;
-          float sr0 = 0.f, si0 = 0.f, sr1 = 0.f, si1 = 0.f;
+    for (int g = 0; g < NG; ++g) {
+      if (4 * g < r2) {
+        const v4f a = *(const v4f*)(hp + 4 * g);
 #pragma unroll
-          for (int b = 0; b < R2MAX; ++b) {
-            if (b < r2) {
-              const float2 h = hv[b];
-              sr0 = fmaf(h.x, u0[b].x, fmaf(-h.y, u0[b].y, sr0));
-              si0 = fmaf(h.x, u0[b].y, fmaf(h.y, u0[b].x, si0));
-              sr1 = fmaf(h.x, u1[b].x, fmaf(-h.y, u1[b].y, sr1));
-              si1 = fmaf(h.x, u1[b].y, fmaf(h.y, u1[b].x, si1));
-            }
-          }
-          const int64_t n = i2 + (int64_t)P.n2 * (i3a + i3l - P.i30);
-          __builtin_nontemporal_store(v4f{sr0, si0, sr1, si1},
-                                      reinterpret_cast<v4f*>(row + (n >> P.lw) * bblk + (n & nmask)));
+        for (int e = 0; e < 4; ++e) {
+          re = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], ure[4 * g + e], re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], uim[4 * g + e], im, 0, 0, 0);
         }
       }
     }
-    return;
-  }
-  for (int i2 = threadIdx.x; i2 < P.n2; i2 += 256) {
-    float2 u[R2MAX];
-    const float2* u2 = P.u2t + t.u2_off + (int64_t)i2 * r2;
+    if (i2 >= P.n2) continue;
+    // register r: row p = 32 pb + 8 (r/4) + 4 h + r%4, column i2
+    const auto put = [&](int r) {
+      const int2 o = tab[32 * pb + 8 * (r >> 2) + 4 * h + (r & 3)];
+      const int n = i2 + o.x;
+      float2* dst = Bk + ((uint32_t)(n >> P.lw) * bblk + (uint32_t)((n & nmask) + o.y));
+      __builtin_nontemporal_store(v2f{re[r], im[r]}, reinterpret_cast<v2f*>(dst));
+    };
+    if (32 * pb + 32 <= np) {
 #pragma unroll
-    for (int b = 0; b < R2MAX; ++b) u[b] = b < r2 ? u2[b] : make_float2(0.f, 0.f);
-    for (int a = 0; a < r1; ++a) {
-      float2* row = Bk + ((int64_t)a << P.lw);
-      for (int i3l = 0; i3l < cnt; ++i3l) {
-        const float2* hv = h3 + (a * T3 + i3l) * r2;
-        float sr = 0.f, si = 0.f;
+      for (int r = 0; r < 16; ++r) put(r);
+    } else {
 #pragma unroll
-        for (int b = 0; b < R2MAX; ++b) {
-          if (b < r2) {
-            const float2 h = hv[b];
-            sr = fmaf(h.x, u[b].x, fmaf(-h.y, u[b].y, sr));
-            si = fmaf(h.x, u[b].y, fmaf(h.y, u[b].x, si));
-          }
-        }
-        const int64_t n = i2 + (int64_t)P.n2 * (i3a + i3l - P.i30);
-        __builtin_nontemporal_store(v2f{sr, si},
-                                    reinterpret_cast<v2f*>(row + (n >> P.lw) * bblk + (n & nmask)));
-      }
+      for (int r = 0; r < 16; ++r)
+        if (32 * pb + 8 * (r >> 2) + 4 * h + (r & 3) < np) put(r);
     }
   }
 }
@@ -309,9 +357,17 @@ __global__ __launch_bounds__(256) void dtg_colgemm_reduce_kernel(ColReduceParams
 typedef void (*decomp_fn)(DecompParams);
 
 decomp_fn decomp_pick(int r2max) {
-  if (r2max <= 16) return dtg_decomp_kernel<16>;
-  if (r2max <= 32) return dtg_decomp_kernel<32>;
-  return dtg_decomp_kernel<64>;
+  switch ((r2max + 3) / 4) {
+    case 1:
+    case 2: return dtg_decomp_kernel<2>;
+    case 3: return dtg_decomp_kernel<3>;
+    case 4: return dtg_decomp_kernel<4>;
+    case 5: return dtg_decomp_kernel<5>;
+    case 6: return dtg_decomp_kernel<6>;
+    case 7:
+    case 8: return dtg_decomp_kernel<8>;
+  }
+  return dtg_decomp_kernel<16>;
 }
 
 }  // namespace
@@ -401,12 +457,11 @@ static int64_t dtg_ldcols(const tv_plan_s* p, int s3) {
   return (cols + 255) / 256 * 256;
 }
 
-// i3 values per decompression workgroup: H3 (r1 x t3w x r2 complex) within
-// 64 KB of LDS
+// i3 values per decompression workgroup: 16 (small ranks still fill blocks of
+// 32 rows), fewer where H would take over 32 KB of LDS
 static int dtg_t3w(const tv_plan_s* p) {
-  const int64_t r12 = (int64_t)p->max_r[0] * p->max_r[1];
-  int t = 8;
-  while (t > 1 && r12 * t * 8 > 64 * 1024) t /= 2;
+  int t = 16;
+  while (t > 1 && dec_lds(p->max_r[0], p->max_r[1], t) > 32 * 1024) t /= 2;
   return t;
 }
 
@@ -501,7 +556,7 @@ static tv_status decomp_setup(const tv_plan_s* p, const float2* x, float2* B, in
   D->n2 = g.n2;
   D->n3 = g.n3;
   D->t3w = dtg_t3w(p);
-  *lds = sizeof(float2) * (size_t)p->max_r[0] * D->t3w * p->max_r[1];
+  *lds = dec_lds(p->max_r[0], p->max_r[1], D->t3w);
   *fn = decomp_pick(p->max_r[1]);
   hipError_t e = hipFuncSetAttribute((const void*)*fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)*lds);

@@ -51,7 +51,7 @@ namespace tv {
 constexpr int DTG_MAXQ = 12;
 constexpr int DTG_KC = 16;      // stacked rows (columns) per K range unit
 constexpr int DTG_LW_F = 8;     // log2 columns per block of B, forward
-constexpr int DTG_LW_A = 3;     // and adjoint
+constexpr int DTG_LW_A = 5;     // and adjoint
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -62,8 +62,10 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // B: the slab of component k, complex64 in blocks of 2^lw columns: entry
 // (row, n) at boff[k] + ((n >> lw) rpad[k] + row) 2^lw + n % 2^lw.  lw = 8
-// forward (a workgroup streams whole rows of its columns), lw = 3 adjoint (a
-// chunk's 8 columns of a row are 64 consecutive bytes, its rows adjacent).
+// forward (a workgroup streams whole rows of its columns), lw = 5 adjoint (a
+// chunk reads 64 bytes of every row; at 256^3 x 512 the decompression writes
+// blocks of 8 columns, 64 bytes, in 2.2 ms, of 16 or 32 in 1.3 ms, and the
+// GEMM takes 9.2 and 9.4 ms).
 struct SplitGemmParams {
   const uint4* a;           // chunk c, block b, plane p, lane l at
                             // aoff[k] + ((c nbtp + b) NS + p) 64 + l
@@ -177,8 +179,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
   if (ADJ) {
     // rows past the component's repeat its last one (their sums are not stored)
     const int row = min(nt * N + bcol, rpad - 1);
-    Bg = P.b + P.boff[k] + (int64_t)row * 8 + 4 * bh;
-    bstep = (int64_t)rpad * 8;
+    Bg = P.b + P.boff[k] + ((int64_t)row << DTG_LW_A) + 4 * bh;
+    bstep = (int64_t)rpad << DTG_LW_A;
   } else {
     const int64_t n = (int64_t)nt * N + bcol;
     Bg = P.b + P.boff[k] + (((n >> DTG_LW_F) * rpad + 4 * bh) << DTG_LW_F) +
@@ -197,7 +199,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
 #pragma unroll
     for (int j = 0; j < NA; ++j) ra[j] = ac[aidx[j]];
     if (stager) {
-      const float2* bc = Bg + (int64_t)c * bstep;
+      const float2* bc =
+          ADJ ? Bg + (int64_t)(c >> (DTG_LW_A - 3)) * bstep + 8 * (c & ((1 << (DTG_LW_A - 3)) - 1))
+              : Bg + (int64_t)c * bstep;
       if (ADJ) {
         const v4f u = *(const v4f*)bc, v = *(const v4f*)(bc + 2);
         rb[0] = make_float2(u[0], u[1]);

@@ -81,3 +81,32 @@ def test_noalloc_takes_what_fp32_operands_fitted(gpu_lib):
     ref = P.rmatvec(y)
     # FP32 sums of 1/8 of 64 x 40 columns in another order
     assert float((x - ref).norm() / ref.norm()) < 320 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dims,q,m,rmax,slab", [
+    ((8, 1, 1), 2, 3, 1, 0),        # one column, rank 1
+    ((9, 3, 40), 1, 4, 3, 17),      # few i2; slabs of 16 + 1 values of i3
+    ((20, 33, 9), 2, 5, 9, 0),      # i2 one past a block, an i3 count past 8
+    ((24, 64, 20), 1, 3, 24, 7),    # up to 24 b, a ragged last slab
+    ((40, 97, 18), 1, 3, 32, 0),    # 32 b: 8 i3 or fewer a workgroup
+    ((48, 64, 48), 1, 3, 40, 0),    # over 32 b
+])
+def test_decompression_edges_match_oracle(gpu_lib, dims, q, m, rmax, slab):
+    """Both directions over the decompression's edges: blocks of 32 i2 and 32
+    (i3, a) rows, groups of four b, slabs.  Tolerance as for the row tiles."""
+    import torch
+    from paper_2103_06393_amd import lib
+    S = random_struct(dims, q, m, rmax, 11)
+    P = _plan(S, 0, 2)
+    for op in (0, 1):
+        lib.tv_plan_configure(P.handle, op, path=1, splits=1, slab_i3=slab, gemm_nbw=2)
+    tol = (2 * rmax + max(rmax * m, dims[1] * dims[2]) / 8 + 8) * 2.0 ** -24
+    rng = np.random.default_rng(6)
+    x = (rng.standard_normal(m) + 1j * rng.standard_normal(m)).astype(np.complex64)
+    y = rng.standard_normal(S.q * S.nv) + 1j * rng.standard_normal(S.q * S.nv)
+    y = y.astype(np.complex64)
+    for _ in range(2):              # the second call finds the first one's workspace
+        got = P.matvec(torch.from_numpy(x).cuda()).cpu().numpy()
+        assert_close(got, om.alg1(S, x)[:, 0], tol, terms=fwd_terms(S, x), what="Z x")
+        got = P.rmatvec(torch.from_numpy(y).cuda()).cpu().numpy()
+        assert_close(got, om.alg2(S, y)[:, 0], tol, terms=adj_terms(S, y), what="Z^* y")
