@@ -307,8 +307,12 @@ __global__ void dtg_ypack_kernel(YPackParams P) {
 }
 
 // x'_j = sum_k sum_{a < r1} sum_i1 conj(U1_j[i1][a]) sum_s Z_s[row a][i1]
-// over the partials s of every slab and split, in FP64, one workgroup per
-// column j, fixed order
+// over the partials s of every slab and split, in FP64 and a fixed order: one
+// workgroup per column j, its 16 waves share the rows (k, a), a lane per i1.
+// Bound by the reads of Z (and by their latency where m is below the CUs:
+// eight partials' loads are in flight a lane).  128^3, q = 12, 128 columns, 16
+// partials (214 MB): 690 -> 57 us against
+// one thread per i1 over all rows; 64^3 x 256 39 -> 7 us.
 struct ColReduceParams {
   const TensorMeta* meta;
   const int32_t* drow;
@@ -319,39 +323,60 @@ struct ColReduceParams {
   int64_t zsplit, m;
   int q, S, n1;
 };
-__global__ __launch_bounds__(256) void dtg_colgemm_reduce_kernel(ColReduceParams P) {
-  __shared__ double red[2][256];
+constexpr int RED_T = 1024;
+__global__ __launch_bounds__(RED_T) void dtg_colgemm_reduce_kernel(ColReduceParams P) {
+  __shared__ double red[2][RED_T / 64];
   const int64_t j = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double sr = 0.0, si = 0.0;
+  int turn = 0;  // rows go round the waves
   for (int k = 0; k < P.q; ++k) {
     const TensorMeta t = P.meta[(int64_t)k * P.m + j];
-    const int64_t r0 = P.brow[k] + P.drow[(int64_t)k * P.m + j];
-    for (int i1 = threadIdx.x; i1 < P.n1; i1 += 256) {
-      const float2* u = P.u1t + t.u1_off + (int64_t)i1 * t.r1;
-      for (int a = 0; a < t.r1; ++a) {
+    const float2* zk = P.z + (P.brow[k] + P.drow[(int64_t)k * P.m + j]) * P.n1;
+    for (int a = (wave - turn) & (RED_T / 64 - 1); a < t.r1; a += RED_T / 64) {
+      for (int i1 = lane; i1 < P.n1; i1 += 64) {
+        const float2 u = P.u1t[t.u1_off + (int64_t)i1 * t.r1 + a];
+        const float2* z = zk + (int64_t)a * P.n1 + i1;
         double zr = 0.0, zi = 0.0;
-        for (int s = 0; s < P.S; ++s) {
-          const float2 z = P.z[(int64_t)s * P.zsplit + (r0 + a) * P.n1 + i1];
-          zr += z.x;
-          zi += z.y;
+        int s = 0;
+        for (; s + 8 <= P.S; s += 8) {
+          float2 v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = z[(int64_t)(s + e) * P.zsplit];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            zr += v[e].x;
+            zi += v[e].y;
+          }
         }
-        const double ur = u[a].x, ui = u[a].y;
+        for (; s < P.S; ++s) {
+          const float2 v = z[(int64_t)s * P.zsplit];
+          zr += v.x;
+          zi += v.y;
+        }
+        const double ur = u.x, ui = u.y;
         sr += ur * zr + ui * zi;
         si += ur * zi - ui * zr;
       }
     }
+    turn = (turn + t.r1) & (RED_T / 64 - 1);
   }
-  red[0][threadIdx.x] = sr;
-  red[1][threadIdx.x] = si;
+  for (int off = 32; off > 0; off >>= 1) {
+    sr += __shfl_xor(sr, off);
+    si += __shfl_xor(si, off);
+  }
+  if (lane == 0) {
+    red[0][wave] = sr;
+    red[1][wave] = si;
+  }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + off];
-      red[1][threadIdx.x] += red[1][threadIdx.x + off];
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < RED_T / 64; ++w) {
+      sr += red[0][w];
+      si += red[1][w];
     }
-    __syncthreads();
+    P.x[j] = make_float2((float)sr, (float)si);
   }
-  if (threadIdx.x == 0) P.x[j] = make_float2((float)red[0][0], (float)red[1][0]);
 }
 
 typedef void (*decomp_fn)(DecompParams);
@@ -486,12 +511,12 @@ static int64_t col_zsplit(const tv_plan_s* p) { return p->dtg_rows * p->grid.n1;
 
 // column splits of the adjoint GEMM per slab of s3 values of i3: the
 // configured count, raised so that no FP32 accumulation chain spans more than
-// COL_CHAIN_STAGES times 16 columns (2048; the partials meet in FP64)
-constexpr int COL_CHAIN_STAGES = 128;
+// 2048 columns (BF16X3) or 4096 (FP32, which rounds its running sum once per 8
+// columns, not after every product); the partials meet in FP64
 static int chain_splits(const tv_plan_s* p, int s3, int splits) {
   const int64_t nst = ((int64_t)p->grid.n2 * s3 + DTG_KC - 1) / DTG_KC;
-  return (int)std::max<int64_t>(std::max(1, splits),
-                                (nst + COL_CHAIN_STAGES - 1) / COL_CHAIN_STAGES);
+  const int64_t chain = (dtg_planes(p) == 2 ? 2048 : 4096) / DTG_KC;
+  return (int)std::max<int64_t>(std::max(1, splits), (nst + chain - 1) / chain);
 }
 int dtg_colgemm_splits(const tv_plan_s* p, int s3) { return chain_splits(p, s3, p->dtg_split_a); }
 
@@ -723,7 +748,7 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
   R.q = g.q;
   R.S = slab * S;
   R.n1 = g.n1;
-  hipLaunchKernelGGL(dtg_colgemm_reduce_kernel, dim3((unsigned)g.m), dim3(256), 0, st, R);
+  hipLaunchKernelGGL(dtg_colgemm_reduce_kernel, dim3((unsigned)g.m), dim3(RED_T), 0, st, R);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TV_OK : hip_error(e, "adjoint reduction launch");
 }
