@@ -184,7 +184,9 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
 
 /* Launch configuration of one direction of a plan's products (what the
  * autotuner chooses; set-up call, not thread-safe against concurrent
- * products on the same plan).
+ * products on the same plan).  A new plan starts on the path that a rule on
+ * its size picks: path 1, in slabs of at most 4 GiB, from about 0.4 GFLOP (for
+ * tv_rmatvec only where tv_rmatvec_noalloc can run it too).
  *   path 0: the fused kernels (Algorithms 1/2 with decompression inside the
  *     mode-1 product): tile_t2 = i2 extent of a workgroup tile (0: the tile
  *     covering the fewest columns), splits = column-range splits (split-K
@@ -222,7 +224,8 @@ tv_status tv_plan_configure(tv_plan plan, int32_t op, const tv_launch_config* cf
  * adjoint's scratch is a static device array of TV_STATIC_SCRATCH_BYTES per
  * GPU, held until the process ends; a plan configuration needing more
  * (tv_workspace_bytes(plan, 1, nrhs)) returns TV_ERR_WORKSPACE before any
- * device work.  All calls on one GPU share the array: calls that overlap in
+ * device work, except that path 1 takes lower slabs where only its packed y
+ * does not fit (its result then differs from tv_rmatvec's in rounding).  All calls on one GPU share the array: calls that overlap in
  * time on one GPU (different streams or threads) race and must be
  * serialised by the caller.  Every scratch entry a call reads is written
  * earlier in the same call, so nothing carries over between calls. */

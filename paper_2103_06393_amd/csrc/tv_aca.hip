@@ -131,6 +131,7 @@ tv_status tv_aca_workspace_bytes(tv_plan p, int32_t op, int32_t nrhs, size_t* by
   size_t inner = 0;
   tv_status st = tv_workspace_bytes(p, op, nrhs, &inner);
   if (st != TV_OK) return st;
+  if (op == 1 && aca_adjoint_dtg(p)) inner = dtg_workspace_bytes(p, 1);
   *bytes = align256((size_t)8 * p->grid.m * nrhs) + inner;
   return TV_OK;
 }
@@ -165,9 +166,12 @@ tv_status tv_aca_rmatvec(tv_plan p, const void* v, int64_t m, int64_t ldv, const
   const int64_t rc = p->grid.m;
   const size_t off = align256((size_t)8 * rc * nrhs);
   float2* W = (float2*)ws;
-  st = tv_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off, stream);
-  if (st != TV_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  st = aca_adjoint_dtg(p)
+           ? run_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off,
+                         dtg_workspace_bytes(p, 1), true, p->dtg_s3_a, p->dtg_split_a, s)
+           : tv_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off, stream);
+  if (st != TV_OK) return st;
   const int64_t blocks = (m + kThreads - 1) / kThreads;
   hipLaunchKernelGGL(aca_vw_kernel, dim3((unsigned)blocks, (unsigned)nrhs), dim3(kThreads), 0, s,
                      (const float2*)v, m, ldv, (const float2*)W, rc, (float2*)x, ldx);

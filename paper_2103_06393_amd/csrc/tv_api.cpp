@@ -88,6 +88,10 @@ tv_status make_tiling(const tv_grid& g, int t2req, int nbcap, Tiling* T) {
 }
 
 
+size_t fused_adjoint_ws(const tv_plan_s* p) {
+  return (size_t)8 * p->grid.q * p->tiling_a.tiles * p->grid.m;
+}
+
 static tv_status validate_grid(const tv_grid* g) {
   if (!g) return set_error(TV_ERR_INVALID_ARG, "grid is NULL");
   if (g->n1 < 1 || g->n2 < 1 || g->n3 < 1 || g->q < 1 || g->m < 1)
@@ -281,6 +285,42 @@ static void pack_apack_bf(const tv_grid& g, int r1, const double* u1, int nbt, u
       }
 }
 
+// The fused kernels' tile of a new plan, instead of the one covering the
+// fewest columns: the warp-specialised kernels need t2 to be a multiple of 32
+// and run 2 to 4 times faster per covered column than the phased ones, whose
+// mode 3 grows with t3 (adjoint per covered column, us: 81x44x108 x 250, ranks
+// 15 to 18, t2 = 32 1650, 16 3140, 4 7200; 21x33x27 x 37, ranks 4 to 12, t2 =
+// 64 18, 8 23, 4 46; 24x10x90 x 100, ranks 4 to 8, t2 = 32 22, 8 46, 4 43).
+// The adjoint's keeps within the static scratch what was within it.
+static tv_status default_tile(tv_plan_s* p, int op) {
+  Tiling& cur = op == 0 ? p->tiling : p->tiling_a;
+  const int64_t mean_core = p->g_off.back() / ((int64_t)p->grid.q * p->grid.m);
+  const size_t ws0 = fused_adjoint_ws(p);
+  Tiling best = cur;
+  double cost = -1.0;
+  for (int t2 = cur.nwg; t2 >= 2; t2 /= 2) {
+    Tiling T;
+    const tv_status st = make_tiling(p->grid, t2, nb_cap(p, op), &T);
+    if (st != TV_OK) return st;
+    if (fused_lds_bytes(p, T, op == 1) > 160 * 1024) continue;
+    if (op == 1) {
+      const size_t ws = ws0 / cur.tiles * T.tiles;
+      if (ws > ws0 && ws > TV_STATIC_SCRATCH_BYTES) continue;
+    }
+    const double per = ws_supported(p, T, op == 1) ? 1.0
+                       : t2 >= 8                   ? 2.0
+                       : t2 == 4                   ? (mean_core <= 300 ? 2.0 : 3.0)
+                                                   : 4.0;
+    const double c = per * (double)T.tiles * T.t2 * T.t3;
+    if (cost < 0.0 || c < cost) {
+      cost = c;
+      best = T;
+    }
+  }
+  cur = best;
+  return TV_OK;
+}
+
 // Pack the FP64 host factors into the device layouts of the kernels (host
 // side; the device copy is made by tv_plan_bind_arena).
 static tv_status pack_plan(tv_plan_s* p) {
@@ -292,6 +332,7 @@ static tv_status pack_plan(tv_plan_s* p) {
   if (fused_lds_bytes(p, p->tiling, false) > 160 * 1024 ||
       fused_lds_bytes(p, p->tiling_a, true) > 160 * 1024)
     return set_error(TV_ERR_NOT_SUPPORTED, "ranks too large for the LDS tile");
+  if ((st = default_tile(p, 0)) != TV_OK || (st = default_tile(p, 1)) != TV_OK) return st;
   // the stacked A operand is packed for the larger row-block count of the
   // two kernels; blocks past n1 are zero rows
   const int nbt = std::max(p->tiling.nbt, p->tiling_a.nbt);
@@ -363,7 +404,10 @@ static tv_status pack_plan(tv_plan_s* p) {
   p->hp.u3t = std::move(u3t);
   p->hp.apack = std::move(apack);
   p->hp.apack_bf = std::move(apack_bf);
-  if (p->with_dtg && (st = dtg_layout(p, p->hp.meta)) != TV_OK) return st;
+  if (p->with_dtg) {
+    if ((st = dtg_layout(p, p->hp.meta)) != TV_OK) return st;
+    dtg_default(p);
+  }
   p->device_bytes = arena_layout(p, nullptr);
   p->finalized = true;
   return TV_OK;
@@ -976,7 +1020,7 @@ tv_status tv_workspace_bytes(tv_plan p, int32_t op, int32_t nrhs, size_t* bytes)
   else if (op == 0)
     *bytes = p->split_f > 1 ? (size_t)8 * p->split_f * g.q * nv : 0;
   else
-    *bytes = (size_t)8 * g.q * p->tiling_a.tiles * g.m;
+    *bytes = fused_adjoint_ws(p);
   return TV_OK;
 }
 
@@ -1041,7 +1085,7 @@ tv_status tv_matvec(tv_plan p, const void* x, int64_t ldx, int32_t nrhs, void* y
 namespace tv {
 
 tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x, int64_t ldx,
-                      void* ws, size_t ws_bytes, size_t need, int s3, int splits,
+                      void* ws, size_t ws_bytes, size_t need, bool dtg, int s3, int splits,
                       hipStream_t s) {
   const int64_t rows = (int64_t)p->grid.q * p->grid.n1 * p->grid.n2 * p->grid.n3;
   tv_status st = check_call(p, y, ldy, rows, nrhs, x, ldx, p->grid.m, ws, ws_bytes, need);
@@ -1049,7 +1093,7 @@ tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void*
   for (int32_t c = 0; c < nrhs; ++c) {
     const float2* yc = (const float2*)y + (int64_t)c * ldy;
     float2* xc = (float2*)x + (int64_t)c * ldx;
-    if (p->use_dtg[1] && dtg_supported(p)) {
+    if (dtg) {
       st = launch_dtg_adjoint(p, yc, xc, ws, s3, splits, s);
       if (st != TV_OK) return st;
       continue;
@@ -1072,6 +1116,7 @@ extern "C" tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t n
   size_t need = 0;
   tv_status st = tv_workspace_bytes(p, 1, nrhs < 1 ? 1 : nrhs, &need);
   if (st != TV_OK) return st;
-  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need, p->dtg_s3_a, p->dtg_split_a,
+  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need,
+                     p->use_dtg[1] && dtg_supported(p), p->dtg_s3_a, p->dtg_split_a,
                      (hipStream_t)stream);
 }

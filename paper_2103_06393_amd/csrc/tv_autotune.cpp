@@ -195,7 +195,10 @@ extern "C" tv_status tv_plan_configure(tv_plan p, int32_t op, const tv_launch_co
   if (op != 0 && op != 1) return set_error(TV_ERR_INVALID_ARG, "op must be 0 or 1");
   const tv_launch_config keep = current_config(p, op);
   tv_status s = apply_config(p, op, *cfg);
-  if (s != TV_OK) apply_config(p, op, keep);  // keeps the error message of the refusal
+  if (s != TV_OK)
+    apply_config(p, op, keep);  // keeps the error message of the refusal
+  else if (op == 1)
+    p->aca_dtg = false;
   return s;
 }
 
@@ -215,8 +218,10 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     const std::string key = plan_key(p, o);
     auto it = cache.find(key);
     tv_launch_config cached{};
-    if (it != cache.end() && from_vec(it->second, &cached) && apply_config(p, o, cached) == TV_OK)
+    if (it != cache.end() && from_vec(it->second, &cached) && apply_config(p, o, cached) == TV_OK) {
+      if (o == 1) p->aca_dtg = false;
       continue;
+    }
     std::vector<tv_launch_config> cands;
     // fused kernels: (cap, t2) pairs times column splits
     std::vector<int> splits;
@@ -375,6 +380,7 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     }
     tv_status s = apply_config(p, o, best_c);
     if (s != TV_OK) return s;
+    if (o == 1) p->aca_dtg = false;
     cache[key] = to_vec(best_c);
     dirty = true;
   }

@@ -476,6 +476,64 @@ tv_status launch_dtg_pack(const tv_plan_s* p, hipStream_t st) {
 
 bool dtg_supported(const tv_plan_s* p) { return p->dtg_packed && p->grid.q <= DTG_MAXQ; }
 
+// The path of a new plan's products, as created (tv_autotune and
+// tv_plan_configure override it).  A call of this path is three or four
+// launches and streams a slab through memory; the fused kernels take one or
+// two and win on the smallest plans only.  Measured (us, fused / this path,
+// FP32): forward 32^3 x 16 (0.11 GFLOP of mode 1) 22 / 23, 32^3 x 64 (0.45)
+// 42 / 35, 81x44x108 x 250 (38) 1673 / 563; adjoint 32^3 x 16 21 / 33, 64^3 x
+// 16 (0.86, 136 stacked rows) 53 / 55, 32^3 x 64 42 / 38, 256x64x64 x 8 (1.5)
+// 90 / 83, 81x44x108 x 250 1890 / 592.
+// tv_rmatvec_noalloc gives tv_rmatvec's result bit for bit, so where it could
+// run the fused adjoint in its static scratch and not this path, tv_rmatvec
+// stays on the fused adjoint until told otherwise; tv_aca_rmatvec has no such
+// twin and goes by the size alone (aca_dtg).
+// Forward tile 256 columns, k-step splits towards one workgroup per CU with 8
+// chunks each at least (64^3 x 256: 317 -> 165, best of all splits and tiles
+// 163).  Adjoint tiles of 256 stacked rows, or 128 where those pad a seventh
+// less or the rows fit one (two workgroups then share a CU), column splits
+// towards a full chip, 48 columns each at least, 32 at most.  Slabs of at most
+// 4 GiB.
+void dtg_default(tv_plan_s* p) {
+  if (!dtg_supported(p)) return;
+  const tv_grid& g = p->grid;
+  const double gflop = 8e-9 * (double)p->sum_r1 * g.n1 * g.n2 * g.n3;
+  const int64_t rows_k = p->dtg_rows / g.q;
+  const auto pow2 = [](int64_t n, int64_t most) {
+    int s = 1;
+    while (2 * s <= std::min(n, most)) s *= 2;
+    return s;
+  };
+  const int64_t per_i3 = std::max<int64_t>(1, p->dtg_rows * g.n2 * (int64_t)sizeof(float2));
+  const int64_t fit = std::max<int64_t>(1, ((int64_t)4 << 30) / per_i3);
+  const int64_t nslab = (g.n3 + fit - 1) / fit;
+  const int s3 = (int)((g.n3 + nslab - 1) / nslab);
+  p->dtg_s3 = p->dtg_s3_a = s3;
+  p->dtg_nbw = 4;
+  p->dtg_split = pow2(std::min(256 / std::max<int64_t>(1, dtg_launch_tiles(p, s3, 4)),
+                               rows_k / 8 / 8), 16);
+  const int64_t t4 = dtg_colgemm_tiles(p, 4), t2 = dtg_colgemm_tiles(p, 2);
+  p->dtg_nbw_a = rows_k <= 256 || 16 * t4 > 9 * t2 ? 2 : 4;
+  const int64_t tiles = p->dtg_nbw_a == 4 ? t4 : t2, slots = p->dtg_nbw_a == 4 ? 256 : 512;
+  p->dtg_split_a = pow2(std::min(slots / std::max<int64_t>(1, tiles),
+                                 (int64_t)g.n2 * s3 / (3 * DTG_KC)), 32);
+  // FP32 chains of at most 256 columns (512 where the partials of Z would pass
+  // 2 GiB): the fused adjoint sums little in FP32 before its FP64 sum
+  // (81x44x108 x 250, error against 64 bits: fused 3.0e-7, chains of 2400
+  // columns 4.3e-7, 512 3.3e-7, 256 2.9e-7, all in 2.4 to 2.5 ms)
+  if (dtg_planes(p) == 3) {
+    const int64_t cols = (int64_t)g.n2 * s3, z = p->dtg_rows * g.n1 * (int64_t)sizeof(float2);
+    const int64_t chain = z * nslab * ((cols + 255) / 256) <= (int64_t)2 << 30 ? 256 : 512;
+    p->dtg_split_a = (int)std::max<int64_t>(
+        p->dtg_split_a, std::min<int64_t>(64, (cols + chain - 1) / chain));
+  }
+  p->dtg_order_a = 0;
+  p->use_dtg[0] = gflop >= 0.3;
+  p->aca_dtg = gflop >= (rows_k >= 256 ? 0.4 : 1.2);
+  p->use_dtg[1] = p->aca_dtg && (fused_adjoint_ws(p) > TV_STATIC_SCRATCH_BYTES ||
+                                 dtg_workspace_bytes(p, 1) <= TV_STATIC_SCRATCH_BYTES);
+}
+
 // columns of one slab's B (a multiple of the widest tile)
 static int64_t dtg_ldcols(const tv_plan_s* p, int s3) {
   const int64_t cols = (int64_t)p->grid.n2 * s3;

@@ -135,6 +135,7 @@ struct tv_plan_s {
   bool with_dtg = true;             // pack the GEMM operands (FP32 plans)
   bool dtg_packed = false;          // the GEMM operands are part of the plan
   bool use_dtg[2] = {false, false};
+  bool aca_dtg = false;  // tv_aca_rmatvec on the column GEMM where use_dtg[1] is not
   int dtg_s3 = 1 << 30;            // i3 values per slab of B (forward)
   int dtg_s3_a = 1 << 30;          // i3 values per slab of B (adjoint)
   int dtg_order_a = 0;             // adjoint GEMM workgroup order (tv_launch_config)
@@ -194,6 +195,7 @@ int nb_cap(const tv_plan_s* p, int op);
 tv_status set_split(tv_plan_s* p, int op, int S);
 // decompress-then-GEMM forward (tv_dtg.hip)
 tv_status dtg_layout(tv_plan_s* p, const std::vector<TensorMeta>& meta);
+void dtg_default(tv_plan_s* p);  // the path and launch configuration of a new plan
 tv_status launch_dtg_pack(const tv_plan_s* p, hipStream_t st);  // set-up: A_k from the bound U1
 bool dtg_supported(const tv_plan_s* p);
 // 32-row blocks of one decompress-then-GEMM workgroup tile (tv_dtg.hip), of
@@ -214,10 +216,15 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
                              int splits, hipStream_t st);
 // the slab and splits that run the adjoint within a scratch of cap bytes
 bool dtg_adjoint_within(const tv_plan_s* p, size_t cap, int* s3, int* splits);
-// tv_rmatvec after its workspace query (need bytes), with the column-GEMM
-// adjoint in slabs of s3 values of i3 and at least `splits` column splits
+// tv_rmatvec after its workspace query (need bytes): the fused adjoint, or
+// (dtg) the column-GEMM adjoint in slabs of s3 values of i3 and at least
+// `splits` column splits
 tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void* x, int64_t ldx,
-                      void* ws, size_t ws_bytes, size_t need, int s3, int splits, hipStream_t s);
+                      void* ws, size_t ws_bytes, size_t need, bool dtg, int s3, int splits,
+                      hipStream_t s);
+size_t fused_adjoint_ws(const tv_plan_s* p);  // workspace of the fused adjoint
+// whether U^* y of tv_aca_rmatvec runs the column GEMM
+inline bool aca_adjoint_dtg(const tv_plan_s* p) { return p->use_dtg[1] || p->aca_dtg; }
 // an upper bound of the device arena of a plan of grid g whose ranks are at
 // most rmax, without the decompress-then-GEMM operands (the arena of a
 // growable plan of g.m columns)

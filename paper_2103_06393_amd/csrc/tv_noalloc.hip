@@ -46,9 +46,9 @@ extern "C" tv_status tv_rmatvec_noalloc(tv_plan p, const void* y, int64_t ldy, i
   tv_status st = tv_workspace_bytes(p, 1, nrhs, &need);
   if (st != TV_OK) return st;
   int s3 = p->dtg_s3_a, splits = p->dtg_split_a;
-  const bool fits = p->use_dtg[1] && tv::dtg_supported(p)
-                        ? tv::dtg_adjoint_within(p, kScratchBytes, &s3, &splits)
-                        : need <= kScratchBytes;
+  const bool dtg = p->use_dtg[1] && tv::dtg_supported(p);
+  const bool fits =
+      dtg ? tv::dtg_adjoint_within(p, kScratchBytes, &s3, &splits) : need <= kScratchBytes;
   if (!fits) {
     char buf[160];
     snprintf(buf, sizeof buf,
@@ -59,6 +59,6 @@ extern "C" tv_status tv_rmatvec_noalloc(tv_plan p, const void* y, int64_t ldy, i
   void* ws = nullptr;
   if ((st = scratch_ptr(&ws)) != TV_OK) return st;
   // every scratch entry the kernels read is written earlier in the same call
-  return tv::run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, kScratchBytes, kScratchBytes, s3, splits,
-                         (hipStream_t)stream);
+  return tv::run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, kScratchBytes, kScratchBytes, dtg, s3,
+                         splits, (hipStream_t)stream);
 }

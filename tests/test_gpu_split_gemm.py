@@ -110,3 +110,59 @@ def test_decompression_edges_match_oracle(gpu_lib, dims, q, m, rmax, slab):
         assert_close(got, om.alg1(S, x)[:, 0], tol, terms=fwd_terms(S, x), what="Z x")
         got = P.rmatvec(torch.from_numpy(y).cuda()).cpu().numpy()
         assert_close(got, om.alg2(S, y)[:, 0], tol, terms=adj_terms(S, y), what="Z^* y")
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dims,q,m,rmax,kernels,aca", [
+    ((20, 13, 7), 2, 5, 5, (1, 1), False),        # tiny: fused
+    ((24, 4, 90), 3, 12, 4, (0, 0), False),       # a narrow grid: phased fused kernels
+    ((33, 35, 37), 3, 40, 8, (1, 1), False),      # small
+    ((32, 64, 24), 3, 80, 8, (2, 2), True),       # scratch-sized, over 256 rows
+    ((64, 64, 64), 3, 20, 8, (2, 1), False),      # few stacked rows
+    ((160, 64, 64), 3, 24, 8, (2, 1), True),      # adjoint slab past the static scratch
+])
+def test_new_plan_path_agrees_with_fused(gpu_lib, dims, q, m, rmax, kernels, aca, prec):
+    """The path a plan starts with by its size, and its products and the ACA
+    products' against those of the fused kernels' fewest-columns tile on the
+    same plan, three vectors with leading dimensions at once.  Tolerances of
+    the two forms' own tests, added."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import AcaTuckerOperator, TuckerPlan
+    S = random_struct(dims, q, m, rmax, 17)
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S), precision=prec)
+    assert tuple(P.info.kernel) == kernels
+    g = torch.Generator(device="cuda").manual_seed(8)
+    rows = S.q * S.nv
+    A = AcaTuckerOperator(P, torch.randn(S.m + 7, S.m, dtype=torch.complex64, device="cuda",
+                                         generator=g))
+    more = (lib.tv_aca_workspace_bytes(P.handle, 1, 1) -
+            lib.tv_workspace_bytes(P.handle, 1, 1)) > 8 * S.m + 255
+    assert more == (aca and kernels[1] != 2)
+    x = torch.randn(3, S.m + 2, dtype=torch.complex64, device="cuda", generator=g)[:, :S.m].t()
+    v = torch.randn(3, A.m, dtype=torch.complex64, device="cuda", generator=g).t()
+    y = torch.randn(3, rows + 1, dtype=torch.complex64, device="cuda", generator=g)[:, :rows].t()
+    a = P.matvec(x), P.rmatvec(y), A.matvec(v), A.rmatvec(y)
+    for op, cap in ((0, 8), (1, 2)):
+        lib.tv_plan_configure(P.handle, op, path=0, tile_t2=0, splits=1, row_cap=cap)
+    P._ws.clear()
+    A._ws.clear()
+    b = P.matvec(x), P.rmatvec(y), A.matvec(v), A.rmatvec(y)
+    for u, w in zip(a, b):
+        assert float((u - w).norm() / w.norm()) < (2e-4 if prec else 2e-5)
+
+
+@pytest.mark.parametrize("dims,m", [((32, 64, 24), 80), ((64, 64, 64), 80), ((33, 35, 37), 40)])
+def test_noalloc_is_rmatvec_on_a_new_plan(gpu_lib, dims, m):
+    """Bit for bit, on the GEMM path and on the fused one."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    S = random_struct(dims, 3, m, 8, 73)
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
+    y = torch.randn(S.q * S.nv, dtype=torch.complex64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(1))
+    x = torch.empty(S.m, dtype=torch.complex64, device="cuda")
+    lib.tv_rmatvec_noalloc(P.handle, y.data_ptr(), S.q * S.nv, 1, x.data_ptr(), S.m,
+                           torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(x, P.rmatvec(y))
