@@ -32,14 +32,6 @@ __device__ __forceinline__ double2 zfma_conj_a(double2 a, double2 b, double2 c) 
   return c;
 }
 
-// Element (i, o) of the mode-d unfolding: o enumerates the other two indices
-// with the lower one fastest.
-__device__ __forceinline__ int64_t unfold_index(int d, int64_t i, int64_t o, int n1, int n2) {
-  if (d == 0) return i + (int64_t)n1 * o;
-  if (d == 1) return (o % n1) + (int64_t)n1 * i + (int64_t)n1 * n2 * (o / n1);
-  return o + (int64_t)n1 * n2 * i;
-}
-
 // Tile pair index -> (ti, tj) with ti <= tj over `tiles` row tiles.
 __device__ __forceinline__ void gram_pair(int pr, int tiles, int& ti, int& tj) {
   ti = 0;
@@ -62,19 +54,24 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // 32 (w / 2), columns 32 (w % 2), as 2 x 2 blocks of 16 x 16, each with a
 // real and an imaginary accumulator; per 4 columns of the unfolding,
 // Re += Xr_re Xc_re^T + Xr_im Xc_im^T and Im += Xr_im Xc_re^T - Xr_re Xc_im^T
-// (S = Xr Xc^*).
+// (S = Xr Xc^*).  Diagonal tiles load one operand and leave out the blocks
+// below the diagonal (40 of 64 MFMAs), written from their mirror images.
+// Bound by FP64 MFMA (72 TFLOP/s for torch's product here).  A thread's
+// columns of the unfolding advance by 16 a stage, so mode 2's (i1, i3) of a
+// column is kept by addition: dividing anew for every element had taken
+// longer than the products.  32 columns of 128^3, all modes: 11.7 ->
+// 7.6 ms (46 TFLOP/s of the products it forms).
 // With nsplit > 1 the unfolding's columns are cut into nsplit ranges (a
 // multiple of 16 each) and every workgroup writes the whole 64 x 64 partial
 // tile of its range to P, [split][tensor][mode][pair] tiles row-major;
 // gram_reduce_kernel sums them.  grid.x = nsplit * tensors * 3 * tiles
 // (tiles + 1) / 2 with tiles = ceil(nmax / 64).
-__global__ __launch_bounds__(256) void gram_kernel(const double2* __restrict__ A, int ntens,
+__global__ __launch_bounds__(256, 3) void gram_kernel(const double2* __restrict__ A, int ntens,
                                                    int n1, int n2, int n3, int nmax, int nsplit,
                                                    double2* __restrict__ S,
                                                    double2* __restrict__ P) {
   constexpr int OC = 16;
-  __shared__ double2 Xr[64][OC + 1];
-  __shared__ double2 Xc[64][OC + 1];
+  __shared__ double2 X[2][64][OC + 1];
   const int tiles = (nmax + 63) / 64;
   const int pairs = tiles * (tiles + 1) / 2;
   int64_t b = blockIdx.x;
@@ -91,6 +88,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const double2* __restrict__ A
   const int dims[3] = {n1, n2, n3};
   const int n = dims[d];
   if (tj * 64 >= n) return;
+  const bool diag = ti == tj;
   const int64_t nv = (int64_t)n1 * n2 * n3;
   const int64_t no_all = nv / n;
   const int64_t chunk = ((no_all + nsplit - 1) / nsplit + OC - 1) / OC * OC;
@@ -98,88 +96,104 @@ __global__ __launch_bounds__(256) void gram_kernel(const double2* __restrict__ A
   // this workgroup's columns [obase, obase + no) of the unfolding
   const int64_t no = std::max<int64_t>(0, std::min(no_all, obase + chunk) - obase);
   const double2* At = A + (int64_t)t * nv;
-  const int tid = threadIdx.x, lane = tid & 63, wr = (tid >> 6) >> 1, wc = (tid >> 6) & 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1;
   v4d re[2][2], im[2][2];
   for (int u = 0; u < 2; ++u)
     for (int v = 0; v < 2; ++v) {
       re[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
       im[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
     }
-  // element e of a stage: (row i, column oc), coalesced along the unfolding's
-  // contiguous index
-  auto coords = [&](int e, int& i, int& oc) {
-    if (d == 0) {
-      i = e % 64;
-      oc = e / 64;
-    } else {
-      oc = e % OC;
-      i = e / OC;
-    }
-  };
+  // element q of a thread's stage: (row iq(q), column oq(q)), coalesced along
+  // the unfolding's contiguous index: mode 1 a row per lane, the waves on
+  // columns; else a column per 16 threads, 16 rows apart
   constexpr int PER = 64 * OC / 256;  // elements per thread per stage
+  const auto iq = [&](int q) { return d == 0 ? (tid & 63) : (tid >> 4) + 16 * q; };
+  const auto oq = [&](int q) { return d == 0 ? (tid >> 6) + 4 * q : (tid & 15); };
+  const int64_t rstride = d == 0 ? 1 : d == 1 ? n1 : (int64_t)n1 * n2;  // of a row
+  // offset of the thread's next column: d == 0: of oq(0), the others 4 apart;
+  // d == 1: (cm, cd) = (o % n1, o / n1)
+  int64_t o_next = obase + oq(0);
+  int64_t cm = d == 1 ? o_next % n1 : 0, cd = d == 1 ? o_next / n1 : 0;
   double2 pr_r[PER], pr_c[PER];
-  auto gload = [&](int64_t o0) {
+  const auto gload = [&](int64_t o0) {
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-      int i, oc;
-      coords(tid + 256 * q, i, oc);
-      const int64_t o = o0 + oc;
+      const int i = iq(q);
+      const int64_t o = o0 + oq(q);
+      const int64_t co = d == 0 ? (obase + o) * n1
+                                : d == 1 ? cm + (int64_t)n1 * n2 * cd : obase + o;
       const int ir = ti * 64 + i, ic = tj * 64 + i;
-      pr_r[q] = (ir < n && o < no) ? At[unfold_index(d, ir, obase + o, n1, n2)]
-                                   : make_double2(0, 0);
-      pr_c[q] = (ic < n && o < no) ? At[unfold_index(d, ic, obase + o, n1, n2)]
-                                   : make_double2(0, 0);
+      const double2* col = At + co;
+      pr_r[q] = (ir < n && o < no) ? col[ir * rstride] : make_double2(0, 0);
+      if (!diag) pr_c[q] = (ic < n && o < no) ? col[ic * rstride] : make_double2(0, 0);
+    }
+    if (d == 1) {
+      cm += OC;
+      while (cm >= n1) {
+        cm -= n1;
+        ++cd;
+      }
     }
   };
   gload(0);
+  const double2(*Xr)[OC + 1] = X[0];
+  const double2(*Xc)[OC + 1] = diag ? X[0] : X[1];
+  // a diagonal tile's wave below the diagonal and, on it, block (1, 0) idle
+  const bool idle = diag && wr > wc, skip10 = diag && wr == wc;
   for (int64_t o0 = 0; o0 < no; o0 += OC) {
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-      int i, oc;
-      coords(tid + 256 * q, i, oc);
-      Xr[i][oc] = pr_r[q];
-      Xc[i][oc] = pr_c[q];
+      X[0][iq(q)][oq(q)] = pr_r[q];
+      if (!diag) X[1][iq(q)][oq(q)] = pr_c[q];
     }
     __syncthreads();
     if (o0 + OC < no) gload(o0 + OC);
+    if (!idle) {
 #pragma unroll
-    for (int ks = 0; ks < OC; ks += 4) {
-      const int kk = ks + (lane >> 4), rr = lane & 15;
-      double2 a[2], c[2];
-      for (int u = 0; u < 2; ++u) a[u] = Xr[32 * wr + 16 * u + rr][kk];
-      for (int v = 0; v < 2; ++v) c[v] = Xc[32 * wc + 16 * v + rr][kk];
-      for (int u = 0; u < 2; ++u)
-        for (int v = 0; v < 2; ++v) {
-          re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, c[v].x, re[u][v], 0, 0, 0);
-          re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, c[v].y, re[u][v], 0, 0, 0);
-          im[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, c[v].x, im[u][v], 0, 0, 0);
-          im[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].x, c[v].y, im[u][v], 0, 0, 0);
-        }
+      for (int ks = 0; ks < OC; ks += 4) {
+        const int kk = ks + (lane >> 4), rr = lane & 15;
+        double2 a[2], c[2];
+        for (int u = 0; u < 2; ++u) a[u] = Xr[32 * wr + 16 * u + rr][kk];
+        for (int v = 0; v < 2; ++v) c[v] = Xc[32 * wc + 16 * v + rr][kk];
+        for (int u = 0; u < 2; ++u)
+          for (int v = 0; v < 2; ++v) {
+            if (u == 1 && v == 0 && skip10) continue;
+            re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, c[v].x, re[u][v], 0, 0, 0);
+            re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, c[v].y, re[u][v], 0, 0, 0);
+            im[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, c[v].x, im[u][v], 0, 0, 0);
+            im[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].x, c[v].y, im[u][v], 0, 0, 0);
+          }
+      }
     }
     __syncthreads();
   }
   // accumulator r of block (u, v): tile element (32 wr + 16 u + lane / 16 + 4 r,
-  // 32 wc + 16 v + lane % 16)
-  if (nsplit > 1) {
-    double2* Pt = P + ((int64_t)sp * ntens * 3 * pairs + tile_id) * 4096;
-    for (int u = 0; u < 2; ++u)
-      for (int v = 0; v < 2; ++v)
-        for (int r = 0; r < 4; ++r)
-          Pt[(32 * wr + 16 * u + (lane >> 4) + 4 * r) * 64 + 32 * wc + 16 * v + (lane & 15)] =
-              make_double2(re[u][v][r], im[u][v][r]);
-    return;
-  }
+  // 32 wc + 16 v + lane % 16); what a diagonal tile left out is written as the
+  // conjugate of its mirror image
+  if (idle) return;
+  double2* Pt = P + ((int64_t)sp * ntens * 3 * pairs + tile_id) * 4096;
   double2* St = S + ((int64_t)d * ntens + t) * nmax * nmax;
   for (int u = 0; u < 2; ++u)
-    for (int v = 0; v < 2; ++v)
+    for (int v = 0; v < 2; ++v) {
+      if (u == 1 && v == 0 && skip10) continue;
+      const bool mirror = diag && (wr < wc || (skip10 && u < v));
       for (int r = 0; r < 4; ++r) {
-        const int i = ti * 64 + 32 * wr + 16 * u + (lane >> 4) + 4 * r;
-        const int j = tj * 64 + 32 * wc + 16 * v + (lane & 15);
-        if (i < n && j < n) {
-          St[(int64_t)i * n + j] = make_double2(re[u][v][r], im[u][v][r]);
-          if (ti != tj) St[(int64_t)j * n + i] = make_double2(re[u][v][r], -im[u][v][r]);
+        const int i = 32 * wr + 16 * u + (lane >> 4) + 4 * r, j = 32 * wc + 16 * v + (lane & 15);
+        const double2 x = make_double2(re[u][v][r], im[u][v][r]);
+        const double2 xc = make_double2(x.x, -x.y);
+        if (nsplit > 1) {
+          Pt[i * 64 + j] = x;
+          if (mirror) Pt[j * 64 + i] = xc;
+        } else {
+          const int gi = ti * 64 + i, gj = tj * 64 + j;
+          if (gi < n && gj < n) {
+            St[(int64_t)gi * n + gj] = x;
+            if (mirror || !diag) St[(int64_t)gj * n + gi] = xc;
+          }
         }
       }
+    }
 }
 
 // Sum of the nsplit partial tiles of gram_kernel, in split order, into S.
@@ -470,12 +484,15 @@ static tv_status last(const char* what) {
 }
 
 // Column ranges of the Gram products: calls with few tensors (a handful of
-// workgroups) cut the unfolding's columns so that about 1024 workgroups run.
+// workgroups) cut the unfolding's columns so that about 1024 workgroups run;
+// between 512 and 2048 workgroups, three or fewer per CU with the off-diagonal
+// tiles last, so that about 4096 do (32 columns of 128^3, 864 workgroups: 9.6
+// -> 8.2 ms; three waves per SIMD instead of two then took it to 7.6).
 int gram_splits(int ntens, int nmax) {
   const int tiles = (nmax + 63) / 64;
   const int64_t base = (int64_t)ntens * 3 * (tiles * (tiles + 1) / 2);
-  if (base >= 512) return 1;
-  return (int)std::min<int64_t>(64, (1024 + base - 1) / base);
+  if (base >= 2048) return 1;
+  return (int)std::min<int64_t>(64, ((base < 512 ? 1024 : 4096) + base - 1) / base);
 }
 
 size_t gram_partial_count(int ntens, int nmax) {
