@@ -229,7 +229,12 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double2* __restr
   if (ti != tj) St[(int64_t)j * n + i] = make_double2(s.x, -s.y);
 }
 
-// Cyclic Jacobi for a Hermitian n x n matrix (n <= 64) in LDS.  Rounds use
+// Cyclic Jacobi for a Hermitian n x n matrix (n <= 64) in LDS, bound by LDS
+// traffic and latency, a workgroup a matrix.  V is held column-major, so that a
+// rotation's lanes, on consecutive rows, meet no bank conflict (row-major, all
+// 64 lanes hit the same banks), and the rotations of the next round are formed
+// beside V's update.  96 matrices of order 64: 1570 -> 705 us, 9 of Algorithm
+// 3's step (44 and 64) 960 -> 630.  Rounds use
 // the round-robin pairing, so the n/2 rotations of a round touch disjoint
 // rows/columns and are applied together as A <- J^* A J, V <- V J, where J
 // is block diagonal over the round's pairs.  Entry (a, b) of A J depends only
@@ -266,10 +271,10 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(JacobiBatch B) {
   const int np = n + (n & 1);
   const int half = np / 2;
   double2* A = jsm;              // n x n, row-major
-  double2* V = A + n * n;        // n x n
-  double2* prm = V + n * n;      // per pair: (c, s), (cos phi, sin phi)
-  int2* pij = reinterpret_cast<int2*>(prm + 64);     // per pair: (i, j or -1)
-  double* red = reinterpret_cast<double*>(pij + 32);  // [2][JT / 64]
+  double2* V = A + n * n;        // n x n, column-major: a rotation's lanes are on consecutive rows
+  double2* prm2 = V + n * n;     // [2 rounds] (c, s) of 32 pairs, then their (cos phi, sin phi)
+  int2* pij2 = reinterpret_cast<int2*>(prm2 + 128);  // [2] per pair: (i, j or -1)
+  double* red = reinterpret_cast<double*>(pij2 + 64);  // [2][JT / 64]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double2* Sm = S + mat * stride;
   for (int e = tid; e < n * n; e += JT) {
@@ -277,6 +282,43 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(JacobiBatch B) {
     V[e] = make_double2((e / n) == (e % n) ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
+  double skip2 = 0.0;
+  // the pairs of a round and their rotations, one lane each
+  const auto rotations = [&](int round, int slot) {
+    if (tid >= half) return;
+    int i, j;
+    if (tid == 0) {
+      i = np - 1;
+      j = round;
+    } else {
+      i = (round + tid) % (np - 1);
+      j = (round - tid + (np - 1)) % (np - 1);
+    }
+    if (i > j) {
+      const int tmp = i;
+      i = j;
+      j = tmp;
+    }
+    double c = 1.0, s = 0.0, cp = 1.0, sp = 0.0;
+    if (j < n) {
+      const double2 aij = A[i * n + j];
+      const double d2 = aij.x * aij.x + aij.y * aij.y;
+      const double aii = A[i * n + i].x, ajj = A[j * n + j].x;
+      const double dd = sqrt(d2);
+      if (dd > 1e-300 && d2 > 1e-34 * fabs(aii * ajj) && d2 > skip2) {
+        const double inv = 1.0 / dd;
+        cp = aij.x * inv;
+        sp = aij.y * inv;
+        const double tau = (ajj - aii) * (0.5 * inv);
+        const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+        c = 1.0 / sqrt(1.0 + tt * tt);
+        s = tt * c;
+      }
+    }
+    prm2[64 * slot + tid] = make_double2(c, s);
+    prm2[64 * slot + 32 + tid] = make_double2(cp, sp);
+    pij2[32 * slot + tid] = make_int2(i, j < n ? j : -1);
+  };
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
     double off = 0.0, dia = 0.0;
     for (int e = tid; e < n * n; e += JT) {
@@ -303,54 +345,23 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(JacobiBatch B) {
     // (Gram matrices of low multilinear rank have many near-zero diagonal
     // entries, where a threshold relative to sqrt(a_ii a_jj) never settles);
     // the sweeps end once every off-diagonal entry is below that
-    const double skip2 = 1e-30 * (offs + dias);
+    skip2 = 1e-30 * (offs + dias);
     const bool done = !(offs > (double)n * n * skip2);
     __syncthreads();
     if (done) break;
+    if (wv == 0) rotations(0, 0);
+    __syncthreads();
     for (int round = 0; round < np - 1; ++round) {
-      if (tid < half) {
-        int i, j;
-        if (tid == 0) {
-          i = np - 1;
-          j = round;
-        } else {
-          i = (round + tid) % (np - 1);
-          j = (round - tid + (np - 1)) % (np - 1);
-        }
-        if (i > j) {
-          const int tmp = i;
-          i = j;
-          j = tmp;
-        }
-        double c = 1.0, s = 0.0, cp = 1.0, sp = 0.0;
-        if (j < n) {
-          const double2 aij = A[i * n + j];
-          const double d2 = aij.x * aij.x + aij.y * aij.y;
-          const double aii = A[i * n + i].x, ajj = A[j * n + j].x;
-          const double dd = sqrt(d2);
-          if (dd > 1e-300 && d2 > 1e-34 * fabs(aii * ajj) && d2 > skip2) {
-            const double inv = 1.0 / dd;
-            cp = aij.x * inv;
-            sp = aij.y * inv;
-            const double tau = (ajj - aii) * (0.5 * inv);
-            const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            s = tt * c;
-          }
-        }
-        prm[2 * tid] = make_double2(c, s);
-        prm[2 * tid + 1] = make_double2(cp, sp);
-        pij[tid] = make_int2(i, j < n ? j : -1);
-      }
-      __syncthreads();
+      const double2* prm = prm2 + 64 * (round & 1);
+      const int2* pij = pij2 + 32 * (round & 1);
       // 2 x 2 blocks: A_pq <- J_p^* A_pq J_q; a pair with no partner (odd n)
       // holds one index and no rotation
       for (int e = tid; e < half * half; e += JT) {
         const int p = e / half, q = e % half;
         const int2 Pp = pij[p], Pq = pij[q];
         const int ip = Pp.x, jp = Pp.y, iq = Pq.x, jq = Pq.y;
-        const double2 csq = prm[2 * q], eq = prm[2 * q + 1];
-        const double2 csp = prm[2 * p], ep = prm[2 * p + 1];
+        const double2 csq = prm[q], eq = prm[32 + q];
+        const double2 csp = prm[p], ep = prm[32 + p];
         const double cq = csq.x, sq = csq.y, cpq = eq.x, spq = eq.y;
         // columns: (x, y) -> (c x - s e^{-i phi} y, s x + c e^{-i phi} y)
         const double2 m1 = make_double2(-sq * cpq, sq * spq);
@@ -372,28 +383,34 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(JacobiBatch B) {
           if (jq >= 0) A[jp * n + jq] = jrot(spp, Y0, n2, Y1);
         }
       }
-      // V <- V J
-      for (int e = tid; e < half * n; e += JT) {
-        const int q = e / n, r = e % n;
-        const int2 Pq = pij[q];
-        if (Pq.y < 0) continue;
-        const double2 cs = prm[2 * q], ph = prm[2 * q + 1];
-        const double2 m1 = make_double2(-cs.y * ph.x, cs.y * ph.y);
-        const double2 m2 = make_double2(cs.x * ph.x, -cs.x * ph.y);
-        const double2 x = V[r * n + Pq.x], y = V[r * n + Pq.y];
-        V[r * n + Pq.x] = jrot(cs.x, x, m1, y);
-        V[r * n + Pq.y] = jrot(cs.y, x, m2, y);
+      __syncthreads();
+      // the first wave forms the next round's rotations (a chain of FP64 square
+      // roots and divisions) while the others apply this one's to V
+      if (wv == 0) {
+        if (round + 2 < np) rotations(round + 1, (round + 1) & 1);
+      } else {
+        for (int e = tid - 64; e < half * n; e += JT - 64) {
+          const int q = e / n, r = e % n;
+          const int2 Pq = pij[q];
+          if (Pq.y < 0) continue;
+          const double2 cs = prm[q], ph = prm[32 + q];
+          const double2 m1 = make_double2(-cs.y * ph.x, cs.y * ph.y);
+          const double2 m2 = make_double2(cs.x * ph.x, -cs.x * ph.y);
+          const double2 x = V[Pq.x * n + r], y = V[Pq.y * n + r];
+          V[Pq.x * n + r] = jrot(cs.x, x, m1, y);
+          V[Pq.y * n + r] = jrot(cs.y, x, m2, y);
+        }
       }
       __syncthreads();
     }
   }
   for (int i = tid; i < n; i += JT) W[mat * wstride + i] = A[i * n + i].x;
   double2* Vm = Vout + mat * vstride;
-  for (int e = tid; e < n * n; e += JT) Vm[e] = V[e];
+  for (int e = tid; e < n * n; e += JT) Vm[e] = V[(e % n) * n + e / n];
 }
 
 size_t jacobi_lds_bytes(int n) {
-  return 16 * (size_t)2 * n * n + 16 * 64 + 8 * 32 + 8 * 2 * (JT / 64);
+  return 16 * (size_t)2 * n * n + 16 * 128 + 8 * 64 + 8 * 2 * (JT / 64);
 }
 
 // T1[t][a][o] = sum_i1 conj(U1[i1, a]) A[i1 + n1 o]; workgroup = 32 values of
