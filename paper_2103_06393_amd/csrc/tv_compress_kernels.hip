@@ -431,10 +431,13 @@ __global__ __launch_bounds__(256) void proj1_kernel(const double2* __restrict__ 
   const double2* U = u1 + u1off[t];
   const int tid = threadIdx.x;
   const int ol = tid % 32, ag = tid / 32;  // a = ag + 8 q
+  // groups of 8 a that the tensor has (all 64 took 2.7 ms over 32 columns of
+  // 128^3 with ranks near 8; now 1.1)
+  const int nq = (r1 + 7) >> 3;
   double2 acc[8];
   for (int q = 0; q < 8; ++q) acc[q] = make_double2(0.0, 0.0);
   for (int i0 = 0; i0 < n1; i0 += 32) {
-    for (int e = tid; e < 32 * 64; e += 256) {
+    for (int e = tid; e < 32 * 8 * nq; e += 256) {
       const int i = e % 32, a = e / 32;
       Us[i][a] = (i0 + i < n1 && a < r1) ? U[(i0 + i) + (int64_t)n1 * a] : make_double2(0, 0);
     }
@@ -444,9 +447,11 @@ __global__ __launch_bounds__(256) void proj1_kernel(const double2* __restrict__ 
                                               : make_double2(0, 0);
     }
     __syncthreads();
-    for (int i = 0; i < 32; ++i) {
-      const double2 av = As[i][ol];
-      for (int q = 0; q < 8; ++q) acc[q] = zfma_conj_a(Us[i][ag + 8 * q], av, acc[q]);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (q < nq)
+#pragma unroll 8
+        for (int i = 0; i < 32; ++i) acc[q] = zfma_conj_a(Us[i][ag + 8 * q], As[i][ol], acc[q]);
     }
     __syncthreads();
   }
@@ -663,14 +668,36 @@ __global__ __launch_bounds__(256) void zgemm_batched_kernel(
 // column, in place on Z (n x l, row-major).  A column whose norm falls below
 // 1e-13 of its norm before projection lies in the span of the previous
 // ones and is set to zero.  One workgroup per matrix.
+// Latency-bound, a chain of 2 l projections (4 waves with a thread per row took
+// 6.6 us a column).  16 waves share each: wave w the dot products of columns 4 w
+// .. 4 w + 3, 16 lanes each over the rows (summed across lanes by DPP: no
+// second barrier), then 8 lanes a row the update.  The columns' norms before
+// projection come first, all at once.  64 columns, n = 81 and 108: 420 ->
+// 290 us; n = 128, which then ran from global memory, 1270 -> 605.
+constexpr int CGS_T = 1024;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// sum over aligned groups of 8 (16) lanes, in every lane: exchanges within
+// quads (lanes 1, 2 apart), then with the mirrored lane of 8 (16)
+__device__ __forceinline__ double sum8(double v) {
+  return dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v)));
+}
+__device__ __forceinline__ double sum16(double v) { return dpp_add<0x140>(sum8(v)); }
+
 template <bool INLDS>
-__global__ __launch_bounds__(256) void cgs2_kernel(Cgs2Batch B) {
-  // with INLDS the matrix is staged in LDS (rows padded by one value, so a
-  // thread per row reading along its row meets no bank conflict)
+__global__ __launch_bounds__(CGS_T) void cgs2_kernel(Cgs2Batch B) {
+  // with INLDS the matrix is staged in LDS (rows padded by one value, so
+  // lanes on consecutive rows meet no bank conflict)
   extern __shared__ double2 zs[];
   __shared__ double2 c[64];
-  __shared__ double2 cpart[4][64];
-  __shared__ double red[2][4];
+  __shared__ double norm0[64];
+  __shared__ double2 red[2][CGS_T / 128];  // one double per wave
   int64_t mat = blockIdx.x;
   int gi = 0;
   while (gi + 1 < B.ng && mat >= B.g[gi].nmat) {
@@ -683,77 +710,79 @@ __global__ __launch_bounds__(256) void cgs2_kernel(Cgs2Batch B) {
   double2* Zb = INLDS ? zs : Zg;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (INLDS) {
-    for (int e = tid; e < n * l; e += 256) zs[(e / l) * ls + e % l] = Zg[e];
+    for (int e = tid; e < n * l; e += CGS_T) zs[(e / l) * ls + e % l] = Zg[e];
     __syncthreads();
   }
-  // workgroup sum of one value per thread (every thread calls it); the two
-  // slots alternate, so one barrier per sum suffices
-  int slot = 0;
-  auto block_sum = [&](double v) -> double {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == 0) red[slot][wv] = v;
-    __syncthreads();
-    const double s = (red[slot][0] + red[slot][1]) + (red[slot][2] + red[slot][3]);
-    slot ^= 1;
-    return s;
-  };
-  // Each thread owns rows i = tid, tid + 256, ... of the column being
-  // orthogonalized: it updates, measures and scales only those, so the
-  // barriers order just the cross-row reads (the projections' dot products).
+  const int kd = tid >> 4, part = tid & 15;  // dot products: column, rows part mod 16
+  const int own = tid >> 3, kp = tid & 7;    // update: row, columns kp mod 8
+  // squared norms of all columns before their projection
+  {
+    double s = 0.0;
+    if (kd < l)
+      for (int i = part; i < n; i += 16) {
+        const double2 v = Zb[(int64_t)i * ls + kd];
+        s += v.x * v.x + v.y * v.y;
+      }
+    s = sum16(s);
+    if (part == 0) norm0[kd] = s;
+  }
+  __syncthreads();
   for (int j = 0; j < l; ++j) {
     double s = 0.0;
-    for (int i = tid; i < n; i += 256) {
-      const double2 v = Zb[(int64_t)i * ls + j];
-      s += v.x * v.x + v.y * v.y;
-    }
-    const double nrm0 = sqrt(block_sum(s));
-    s = 0.0;
     for (int pass = 0; pass < 2; ++pass) {
-      // c[k] = sum_i conj(Q[i,k]) z[i] for k < j: thread (part, kk) sums the
-      // rows i = part mod 4, then the four parts are added in order
-      {
-        const int kk = tid & 63, part = tid >> 6;
+      // c[k] = sum_i conj(Q[i,k]) z[i] for k < j
+      if ((kd & ~3) < j) {
         double2 a = make_double2(0.0, 0.0);
-        // unrolled so that the loads of several rows are in flight at once
-        // (the sums keep their order)
-        if (kk < j)
+        const int k = min(kd, l - 1);
 #pragma unroll 8
-          for (int i = part; i < n; i += 4) {
-            const double2 q = Zb[(int64_t)i * ls + kk], z = Zb[(int64_t)i * ls + j];
-            a.x += q.x * z.x + q.y * z.y;  // conj(q) z
-            a.y += q.x * z.y - q.y * z.x;
-          }
-        cpart[part][kk] = a;
+        for (int i = part; i < n; i += 16) {
+          const double2 q = Zb[(int64_t)i * ls + k], z = Zb[(int64_t)i * ls + j];
+          a = zfma_conj_a(q, z, a);
+        }
+        a.x = sum16(a.x);
+        a.y = sum16(a.y);
+        if (part == 0 && kd < j) c[kd] = a;
       }
       __syncthreads();
-      if (tid < j)
-        c[tid] = make_double2(cpart[0][tid].x + cpart[1][tid].x + cpart[2][tid].x + cpart[3][tid].x,
-                              cpart[0][tid].y + cpart[1][tid].y + cpart[2][tid].y + cpart[3][tid].y);
-      __syncthreads();
-      for (int i = tid; i < n; i += 256) {
-        double2 z = Zb[(int64_t)i * ls + j];
+      // the first lane of a row updates and measures it
+      for (int i = own; i < n; i += CGS_T / 8) {
+        double2 z = make_double2(0.0, 0.0);
 #pragma unroll 8
-        for (int k = 0; k < j; ++k) {
+        for (int k = kp; k < j; k += 8) {
           const double2 q = Zb[(int64_t)i * ls + k], ck = c[k];
-          z.x -= q.x * ck.x - q.y * ck.y;
-          z.y -= q.x * ck.y + q.y * ck.x;
+          z.x = fma(q.x, ck.x, fma(-q.y, ck.y, z.x));
+          z.y = fma(q.x, ck.y, fma(q.y, ck.x, z.y));
         }
-        Zb[(int64_t)i * ls + j] = z;
-        if (pass == 1) s += z.x * z.x + z.y * z.y;
+        z.x = sum8(z.x);
+        z.y = sum8(z.y);
+        if (kp == 0) {
+          const double2 v = Zb[(int64_t)i * ls + j];
+          z = make_double2(v.x - z.x, v.y - z.y);
+          Zb[(int64_t)i * ls + j] = z;
+          if (pass == 1) s += z.x * z.x + z.y * z.y;
+        }
       }
       if (pass == 0) __syncthreads();
     }
-    const double nrm = sqrt(block_sum(s));
-    const double scale = (nrm > 1e-13 * nrm0 && nrm > 1e-300) ? 1.0 / nrm : 0.0;
-    for (int i = tid; i < n; i += 256) {
-      const double2 v = Zb[(int64_t)i * ls + j];
-      Zb[(int64_t)i * ls + j] = make_double2(v.x * scale, v.y * scale);
-    }
-  }
-  if (INLDS) {
+    // the column's norm: lanes 0, 8, .. 56 of every wave hold sums
+    s = sum16(s);
+    const double t = __shfl(s, 0) + __shfl(s, 16) + __shfl(s, 32) + __shfl(s, 48);
+    if (lane == 0) reinterpret_cast<double*>(red[j & 1])[wv] = t;
     __syncthreads();
-    for (int e = tid; e < n * l; e += 256) Zg[e] = zs[(e / l) * ls + e % l];
+    double nrm = 0.0;
+#pragma unroll
+    for (int w = 0; w < CGS_T / 128; ++w) nrm += red[j & 1][w].x + red[j & 1][w].y;
+    nrm = sqrt(nrm);
+    const double scale = (nrm > 1e-13 * sqrt(norm0[j]) && nrm > 1e-300) ? 1.0 / nrm : 0.0;
+    if (kp == 0)
+      for (int i = own; i < n; i += CGS_T / 8) {
+        const double2 v = Zb[(int64_t)i * ls + j];
+        Zb[(int64_t)i * ls + j] = make_double2(v.x * scale, v.y * scale);
+      }
+    __syncthreads();  // the next column's dot products read this one
   }
+  if (INLDS)
+    for (int e = tid; e < n * l; e += CGS_T) Zg[e] = zs[(e / l) * ls + e % l];
 }
 
 // Deterministic start block Omega (n x l, row-major, complex entries in
@@ -774,13 +803,17 @@ __global__ void omega_kernel(double2* __restrict__ Om, int n, int l, int64_t str
   Om[b * stride + r] = make_double2(h1 * (2.0 / 4294967296.0) - 1.0, h2 * (2.0 / 4294967296.0) - 1.0);
 }
 
-__global__ void trace_kernel(const double2* __restrict__ S, int n, int64_t stride, int nmat,
-                             double* __restrict__ tr) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nmat) return;
+// a wave per matrix: 64 diagonal entries in flight, added in order
+__global__ __launch_bounds__(64) void trace_kernel(const double2* __restrict__ S, int n,
+                                                   int64_t stride, double* __restrict__ tr) {
+  const double2* Sb = S + blockIdx.x * stride;
   double s = 0.0;
-  for (int i = 0; i < n; ++i) s += S[b * stride + (int64_t)i * n + i].x;
-  tr[b] = s;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + threadIdx.x;
+    const double v = i < n ? Sb[(int64_t)i * n + i].x : 0.0;
+    for (int e = 0; e < min(64, n - i0); ++e) s += __shfl(v, e);
+  }
+  if (threadIdx.x == 0) tr[blockIdx.x] = s;
 }
 
 tv_status launch_zgemm(int trans, int M, int N, int K, const double2* A, int lda, int64_t sA,
@@ -819,13 +852,14 @@ tv_status launch_cgs2(const Cgs2Group* groups, int ng, int l, hipStream_t st) {
     blocks += groups[g].nmat;
   }
   const size_t lds = (size_t)nmax * (l + 1) * sizeof(double2);
-  if (lds <= 128 * 1024) {
+  // with the static arrays within the 160 KB of a CU: n <= 149
+  if (lds <= 152 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)cgs2_kernel<true>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_error(e, "hipFuncSetAttribute(cgs2)");
-    hipLaunchKernelGGL(cgs2_kernel<true>, dim3((unsigned)blocks), dim3(256), lds, st, B);
+    hipLaunchKernelGGL(cgs2_kernel<true>, dim3((unsigned)blocks), dim3(CGS_T), lds, st, B);
   } else {
-    hipLaunchKernelGGL(cgs2_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, B);
+    hipLaunchKernelGGL(cgs2_kernel<false>, dim3((unsigned)blocks), dim3(CGS_T), 0, st, B);
   }
   return last("cgs2_kernel");
 }
@@ -842,8 +876,8 @@ tv_status launch_subspace_prep_batch(const SubspaceJob* jobs, int nj, int nmat, 
     hipLaunchKernelGGL(omega_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, Q[j],
                        n, l, nl, nmat);
     if ((s = last("omega_kernel")) != TV_OK) return s;
-    hipLaunchKernelGGL(trace_kernel, dim3((unsigned)((nmat + 255) / 256)), dim3(256), 0, st,
-                       jobs[j].S, n, jobs[j].sS, nmat, jobs[j].tr);
+    hipLaunchKernelGGL(trace_kernel, dim3((unsigned)nmat), dim3(64), 0, st, jobs[j].S, n,
+                       jobs[j].sS, jobs[j].tr);
     if ((s = last("trace_kernel")) != TV_OK) return s;
   }
   // Z = S Omega, Q = orth(Z); Z = S Q, Q = orth(Z) (two swaps: Q ends in ws),
