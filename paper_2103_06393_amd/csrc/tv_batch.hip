@@ -10,7 +10,7 @@
 // where T holds decompressed tensor values Z^{kj} on the tile's V voxels.
 // Two generations of kernels:
 //  * ranks <= 32: decompression on MFMA as well (batch_mode3, then
-//    batch_fwd_mfma / batch_adj_mfma below), eight waves per workgroup;
+//    batch_fwd_mfma / batch_adj_mfma below), 16 waves per workgroup;
 //  * otherwise wave-local VALU decompression (each wave takes whole
 //    tensors: mode-3 on the core, mode-2 per column, mode-1 per voxel row,
 //    eq. 6/7), two workgroup barriers per step.
@@ -303,28 +303,37 @@ __global__ __launch_bounds__(256) void batch_adj(BatchArgs A) {
 }
 
 // Adjoint epilogue: X_c[j0 + jj][32 g + rl] = sum of the partial blocks of
-// all components and tile slices of (plan, chunk, group), in list order.
-// One workgroup per output block; red_list[b*nper .. (b+1)*nper) are item
-// indices, red_out[b] = {plan, chunk, group}.
-__global__ __launch_bounds__(256) void batch_adj_reduce(BatchArgs A, const int* red_list,
-                                                        const int4* red_out, int nper) {
+// all components and tile slices of (plan, chunk, group).  A workgroup sums
+// 64 of the 1024 elements of output block blockIdx.x: wave w adds every 16th
+// block of the list from w on, then wave 0 the 16 sums, all in list order.
+// Bound by the read of the partial blocks: one workgroup per output block
+// left 21 of 256 CUs reading 32 MB, 0.60 ms; 16 per block take 0.02 ms.
+// red_list[b*nper .. (b+1)*nper) are item indices, red_out[b] = {plan,
+// chunk, group}.
+__global__ __launch_bounds__(1024) void batch_adj_reduce(BatchArgs A, const int* red_list,
+                                                         const int4* red_out, int nper) {
+  __shared__ float2 sum[16][64];
   const int4 O = red_out[blockIdx.x];
   const int* lst = red_list + (int64_t)blockIdx.x * nper;
-  const int64_t m = A.plans[O.x].m;
-  const int64_t j0 = (int64_t)O.y * 32;
-  float2* Xo = A.out[O.x];
-  const int64_t ldx = A.ld_out[O.x];
-  for (int e = threadIdx.x; e < 1024; e += 256) {
-    const int rl = e / 32, jj = e % 32;
-    float2 acc = make_float2(0.f, 0.f);
-    for (int i = 0; i < nper; ++i) {
-      const float2 v = A.partial[(int64_t)lst[i] * 1024 + e];
-      acc.x += v.x;
-      acc.y += v.y;
-    }
-    const int r = O.z * 32 + rl;
-    if (j0 + jj < m && r < A.nrhs[O.x]) Xo[(j0 + jj) + ldx * r] = acc;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = blockIdx.y * 64 + lane;
+  float2 acc = make_float2(0.f, 0.f);
+  for (int i = wave; i < nper; i += 16) {
+    const float2 v = A.partial[(int64_t)lst[i] * 1024 + e];
+    acc.x += v.x;
+    acc.y += v.y;
   }
+  sum[wave][lane] = acc;
+  __syncthreads();
+  if (wave) return;
+#pragma unroll
+  for (int w = 1; w < 16; ++w) {
+    acc.x += sum[w][lane].x;
+    acc.y += sum[w][lane].y;
+  }
+  const int64_t j = (int64_t)O.y * 32 + e % 32;
+  const int r = O.z * 32 + e / 32;
+  if (j < A.plans[O.x].m && r < A.nrhs[O.x]) A.out[O.x][j + A.ld_out[O.x] * r] = acc;
 }
 
 __global__ void reset_counter(int* c) { *c = 0; }
@@ -372,7 +381,7 @@ __device__ __forceinline__ v16f mfma_bf(uint4 a, uint4 b, v16f c) {
 //   H   [i3][ab < nab][q < nq2][lane][4]: step t = 4q + i of lane l holds
 //       Re/Im (s = (l/16)%2) of H[16 ab + l%16][2t + l/32]          (mode 2 A)
 //   U2  [cg][q < nq2][lane][4]: Re/Im (part ^ s) of U2[8 cg + l%8][2t + l/32],
-//       part = (l/8)%2; the sign of -U2i is applied at the MFMA      (mode 2 B)
+//       part = (l/8)%2, with the sign of -U2i                        (mode 2 B)
 //   U1  [ic][q < nq1][lane][4]: Re/Im (s) of U1[16 ic + l%16][2t + l/32]   (mode 1 A)
 
 // Mode 3 for every tensor of the batch and every i3, written in the packed
@@ -425,8 +434,9 @@ __global__ __launch_bounds__(256) void batch_mode3(BatchArgs A, const int2* tlis
 // Operands of one tensor on one tile, loaded a step before they are used:
 // mode-2 A (H) and B (U2 rows c0..c0+7) lane values, x_j for this lane's
 // right-hand side, and what mode 1 needs of the metadata.
+template <int NAB>
 struct DecOps {
-  float ha[2][16];
+  float ha[NAB][16];
   float ub[16];
   float2 xv;
   int r1, r2;
@@ -450,9 +460,6 @@ __device__ __forceinline__ int4 uni_item(int4 v) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t brsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float bload(__amdgpu_buffer_rsrc_t r, int off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
 // four K steps t = 4q .. 4q + 3 of one packed quad block into dst[4q ..]
 __device__ __forceinline__ void bload4(__amdgpu_buffer_rsrc_t r, int off, float* dst) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -464,38 +471,55 @@ __device__ __forceinline__ void bload4(__amdgpu_buffer_rsrc_t r, int off, float*
 }
 #define TV_OOB 0x40000000
 
-// Loads are unconditional and land in their final registers, so the
-// compiler neither branches around them nor waits for each one.  Callers
-// pass an index that is always valid (clamped) and discard what they do not
-// use: every path through a loop then issues the same loads in the same
-// order, which keeps the wait counts exact at the joins.  The x_j load (WX)
-// clamps the right-hand side (lanes beyond nrhs are never stored).
-template <bool WX>
-__device__ __forceinline__ void dec_load(DecOps& o, const BTensor* bt, int64_t j,
-                                         const float* hc, const float* u2p, int i3, int c0,
-                                         const float2* X, int64_t ldx, int xr, int lane) {
-  // read-only for the kernel's lifetime: constant address space, uniform
-  // index, so these are scalar loads (lgkmcnt, no drain of vector loads)
+// nq (1 to 4) quads of a packed operand, 1 KB apart, into dst[0 .. 4 nq - 1].
+// With CND only the quads that a rank fills are loaded; without, all four
+// are issued, the rest out of range (zero), which keeps the code straight
+// and lets 128 registers do.
+template <bool CND>
+__device__ __forceinline__ void load_quads(__amdgpu_buffer_rsrc_t r, int lane, int nq, float* dst) {
+  bload4(r, lane * 16, dst);
+  if constexpr (!CND) {
+#pragma unroll
+    for (int q = 1; q < 4; ++q) bload4(r, q < nq ? lane * 16 + 1024 * q : TV_OOB, dst + 4 * q);
+  } else if (nq > 1) {
+    bload4(r, lane * 16 + 1024, dst + 4);
+    if (nq > 2) {
+      bload4(r, lane * 16 + 2048, dst + 8);
+      if (nq > 3) bload4(r, lane * 16 + 3072, dst + 12);
+    }
+  }
+}
+
+// One tensor's record in scalar registers.  Read-only for the kernel's
+// lifetime: constant address space, uniform index, so these are scalar loads
+// (lgkmcnt, no drain of vector loads).
+__device__ __forceinline__ BTensor bt_load(const BTensor* bt, int64_t j) {
   typedef const __attribute__((address_space(4))) BTensor CBT;
   CBT* T = reinterpret_cast<CBT*>(reinterpret_cast<uintptr_t>(bt)) + j;
-  const int r1 = uni(T->r1), r2 = uni(T->r2);
-  const int64_t h_off = uni64(T->h_off), u2p_off = uni64(T->u2p_off);
-  o.r1 = r1;
-  o.r2 = r2;
-  o.u1p = uni64(T->u1p_off);
-  const int nab = (r1 + 15) >> 4, nq2 = (((r2 + 1) >> 1) + 3) >> 2;
-  // packed H(i3): nab x nq2 blocks; quads beyond are out of range (zero)
+  return BTensor{uni(T->r1), uni(T->r2), uni64(T->h_off), uni64(T->u1p_off), uni64(T->u2p_off)};
+}
+
+// Callers pass an index that is always valid (clamped) and discard what they
+// do not use.  The x_j load (WX) clamps the right-hand side (lanes beyond
+// nrhs are never stored).  The mode-2 row blocks loaded are ab0 ..
+// ab0 + NAB - 1, as far as the tensor has them.
+template <bool WX, bool CND, int NAB>
+__device__ __forceinline__ void dec_load(DecOps<NAB>& o, const BTensor& T, int64_t j,
+                                         const float* hc, const float* u2p, int i3, int c0,
+                                         const float2* X, int64_t ldx, int xr, int ab0, int lane) {
+  o.r1 = T.r1;
+  o.r2 = T.r2;
+  o.u1p = T.u1p_off;
+  const int nab = (T.r1 + 15) >> 4, nq2 = (((T.r2 + 1) >> 1) + 3) >> 2;
+  // packed H(i3): nab x nq2 blocks
   const __amdgpu_buffer_rsrc_t rh =
-      brsrc(hc + h_off + (int64_t)i3 * nab * nq2 * 256, 1024u * nab * nq2);
+      brsrc(hc + T.h_off + ((int64_t)i3 * nab + ab0) * nq2 * 256, 1024u * (nab - ab0) * nq2);
 #pragma unroll
-  for (int ab = 0; ab < 2; ++ab)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      bload4(rh, ab < nab && q < nq2 ? ((ab * nq2 + q) * 64 + lane) * 16 : TV_OOB, &o.ha[ab][4 * q]);
+  for (int ab = 0; ab < NAB; ++ab)
+    if (!CND || ab0 + ab < nab) load_quads<CND>(rh, lane + 64 * ab * nq2, nq2, o.ha[ab]);
   // packed U2 of column group c0 / 8
-  const __amdgpu_buffer_rsrc_t ru = brsrc(u2p + u2p_off + (int64_t)(c0 >> 3) * nq2 * 256, 1024u * nq2);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) bload4(ru, q < nq2 ? (q * 64 + lane) * 16 : TV_OOB, &o.ub[4 * q]);
+  if (!CND || ab0 < nab)
+    load_quads<CND>(brsrc(u2p + T.u2p_off + (int64_t)(c0 >> 3) * nq2 * 256, 1024u * nq2), lane, nq2, o.ub);
   if (WX) o.xv = X[j + ldx * xr];
 }
 
@@ -524,70 +548,83 @@ __device__ __forceinline__ v4f chain16_n(int np, const float* a, const float* b)
   return v4f{0.f, 0.f, 0.f, 0.f};
 }
 
-// Mode 2 on MFMA into the wave's Bc[a][32]: columns f (Re), 8 + f (Im),
-// 16 + f (-Re, unused) and 24 + f (-Im), so that the mode-1 B operand is a
-// plain read.  The U2 operand's sign (-U2i at part 0, s = 1) is applied here.
-__device__ __forceinline__ void dec_mode2(const DecOps& o, float* Bc, int lane) {
+// Mode 2 on MFMA into the tensor's Bc[a][BCS]: columns f (Re), 8 + f (Im) and
+// 16 + f (-Im) of rows 16 ab0 .. 16 (ab0 + NAB) - 1, so that the mode-1 B
+// operand is a plain read.  A row stride of 28 floats puts the four row
+// groups of a store, and the two rows of an operand read, in different banks.
+constexpr int BCS = 28, BCN = 32 * BCS;
+template <int NAB>
+__device__ __forceinline__ void dec_mode2(const DecOps<NAB>& o, float* Bc, int ab0, int lane) {
   const int np2 = (o.r2 + 1) >> 1;
-  const bool neg = ((lane >> 3) & 1) == 0 && ((lane >> 4) & 1) == 1;
-  float ub[16];
 #pragma unroll
-  for (int t = 0; t < 16; ++t) ub[t] = neg ? -o.ub[t] : o.ub[t];
+  for (int ab = 0; ab < NAB; ++ab) {
+    if (16 * (ab0 + ab) < o.r1) {
+      const v4f d = chain16_n(np2, o.ha[ab], o.ub);
+      float* dst = Bc + (16 * (ab0 + ab) + 4 * (lane >> 4)) * BCS + (lane & 15);
 #pragma unroll
-  for (int ab = 0; ab < 2; ++ab) {
-    if (16 * ab < o.r1) {
-      const v4f d = chain16_n(np2, o.ha[ab], ub);
-      float* dst = Bc + (16 * ab + 4 * (lane >> 4)) * 32 + (lane & 15);
+      for (int r = 0; r < 4; ++r) dst[BCS * r] = d[r];
+      if (lane & 8)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        dst[32 * r] = d[r];
-        dst[32 * r + 16] = -d[r];
-      }
+        for (int r = 0; r < 4; ++r) dst[BCS * r + 8] = -d[r];
     }
   }
 }
 
-// Mode-1 B operand (the embedded B = H U2^T) for every K step, from Bc;
-// steps t >= (r1 + 1) / 2 are never issued.
+// Mode-1 B operand (the embedded B = H U2^T, -Bi at part 0, s = 1) for every
+// K step, from Bc; steps t >= (r1 + 1) / 2 are never issued.
 __device__ __forceinline__ void dec_bops(const float* Bc, float* bb, int lane) {
   const int f = lane & 7, part = (lane >> 3) & 1, s = (lane >> 4) & 1;
-  const int col = f + (part == 0 ? (s ? 24 : 0) : (s ? 0 : 8));
+  const float* src = Bc + (lane >> 5) * BCS + f + 8 * (part ^ s) + (part < s ? 8 : 0);
 #pragma unroll
-  for (int t = 0; t < 16; ++t) bb[t] = Bc[(2 * t + (lane >> 5)) * 32 + col];
+  for (int t = 0; t < 16; ++t) bb[t] = src[2 * t * BCS];
 }
 
-// U1 operand of 16-row chunk ic for every K step (packed quads; quads
-// beyond nq1 are out of range and read zero; steps t >= np1 are never
-// issued as MFMAs).  All loads are issued on every path so that the wait
-// counts stay exact.
+// U1 operand of 16-row chunk ic for every K step (packed quads; steps
+// t >= np1 are never issued as MFMAs).
+template <bool CND>
 __device__ __forceinline__ void dec_u1ops(const float* u1p, int64_t off, int r1, int ic,
                                           float* ua, int lane) {
   const int nq1 = (((r1 + 1) >> 1) + 3) >> 2;
-  const __amdgpu_buffer_rsrc_t r = brsrc(u1p + off + (int64_t)ic * nq1 * 256, 1024u * nq1);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) bload4(r, q < nq1 ? (q * 64 + lane) * 16 : TV_OOB, &ua[4 * q]);
+  load_quads<CND>(brsrc(u1p + off + (int64_t)ic * nq1 * 256, 1024u * nq1), lane, nq1, ua);
 }
 
 // Forward, MFMA decompression.  Item = (plan, component, tile of 8 columns
-// at one i3, right-hand-side group of 32); NB1 = n1p32 / 32 <= 3.  Waves
-// 4..7 produce: in step s wave 4 + w decompresses tensor 4s + w into
-// Ts[s&1][w], its operands loaded one step ahead (U1 chunk by chunk as the
-// previous tensor's chunks retire).  Waves 0..3 consume: in step s wave w
-// applies tensors 4(s-1).. to columns 2w, 2w+1 of the tile (2 NB1 blocks of
-// 32 voxels x 32 right-hand sides on v_mfma_f32_32x32x2f32).  One barrier
-// per step.
-template <int NB1, bool BF>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+// at one i3, right-hand-side group of 32); NB1 = n1p32 / 32 <= 3.  The first
+// 4 PS waves consume, the others produce; PS producers share a tensor: in
+// step s waves w and w + 4 of the producers decompress tensor 4s + w into
+// Ts[s&1][w], one row block of its mode 2 and half of its rows each, operands
+// loaded one step ahead.  The consumers apply tensors 4(s-1).. to 2 / PS
+// columns of the tile each (32 voxels x 32 right-hand sides at a time on
+// v_mfma_f32_32x32x2f32).  One barrier per step.
+//
+// Bound by the producers' serial path (record, operand loads, mode 2, LDS,
+// mode 1): with the consumers' MFMAs taken out it still takes 0.8 of the
+// time.  At 96 x 128 x 112 voxels, q = 3, 630 columns of rank 8 to 24 in three
+// plans, 32 right-hand sides: 13.8 ms with one producer a tensor and four
+// waves in each role; 12.8 with PS = 2, the producers ahead in priority and
+// the loads in one order from the first step on (the wait counts at the head
+// of the loop are then exact); 12.3 with -Im stored instead of a sign per
+// read; 11.8 with only the quads in use loaded; 11.3 with right-hand sides
+// along the rows of D, whose stores are 256 contiguous bytes instead of 8.
+// (Matrix cores busy 51 % of the 13.8 ms.)  PS = 2 puts four waves on a SIMD;
+// NB1 = 1 has them with two workgroups of PS = 1 a CU, whose barriers hold up
+// only one of the two: 0.43 ms against 0.47 with PS = 2 at 32 x 64 x 64, q = 3,
+// m = 100, rank 24.  At 64 x 64 x 64, m = 100, rank 32, PS = 2 takes 0.77 ms,
+// before 0.89; BF16X3 at 96 x 64 x 64, 123 columns of rank 16, 0.58, before 0.84.
+template <int NB1, bool BF, int PS>
+__global__ __launch_bounds__(512 * PS) __attribute__((amdgpu_waves_per_eu(2 * PS)))
 void batch_fwd_mfma(BatchArgs A) {
-  constexpr int NPW = 4, N1P = 32 * NB1, V = 8 * N1P, NCH = 2 * NB1, BPC = 2 * NB1;
+  constexpr int NPW = 4, N1S = 32 * NB1 + (BF ? 1 : 4), V = 8 * N1S, NCH = 2 * NB1 / PS,
+                BPC = 2 * NB1 / PS;
   extern __shared__ float4 bsm4[];
   __shared__ int s_item;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const bool producer = wave >= 4;
-  const int w = wave & 3;
+  const bool producer = wave >= 4 * PS;
+  // consumers: w = column group; producers: tensor w, share hw of its rows
+  const int w = producer ? wave & 3 : wave, hw = (wave >> 2) - PS;
   float* Ts = reinterpret_cast<float*>(bsm4);                    // [2][NPW][2][V]
   float2* Xs = reinterpret_cast<float2*>(Ts + 2 * NPW * 2 * V);  // [2][NPW][32]
-  float* Bc = reinterpret_cast<float*>(Xs + 2 * NPW * 32) + w * 1024;  // [2][NPW][1024]
+  float* Bc = reinterpret_cast<float*>(Xs + 2 * NPW * 32) + (wave & 3) * BCN;  // [2][NPW][BCN]
   // The two roles run separate item loops (same items, same barrier count
   // per item), so that neither keeps the other's per-lane constants live.
   if (!producer) {
@@ -602,6 +639,7 @@ void batch_fwd_mfma(BatchArgs A) {
       for (int b = 0; b < BPC; ++b)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[b][0][i] = acc[b][1][i] = 0.f;
+      if constexpr (PS > 1) __syncthreads();
       for (int s = 0; s <= nbat; ++s) {
         if (BF && s > 0) {
           // BF16X3: one v_mfma_f32_32x32x16_bf16 pair per output covers the
@@ -636,55 +674,71 @@ void batch_fwd_mfma(BatchArgs A) {
                                             bt_pack(xr_l[0], xr_l[1]), bt_pack(xr_l[2], xr_l[3]))
                                : make_uint4(0u, 0u, 0u, 0u);
           const uint4* ta = reinterpret_cast<const uint4*>(Ts) + (pb * 2 + (lane >> 5)) * V +
-                            2 * w * N1P + (lane & 31);
+                            (2 / PS) * w * N1S + (lane & 31);
 #pragma unroll
           for (int b = 0; b < BPC; ++b) {
-            const uint4 a = ta[32 * b];
-            acc[b][0] = mfma_bf(a, b1r, acc[b][0]);
-            acc[b][0] = mfma_bf(a, b2r, acc[b][0]);
-            acc[b][1] = mfma_bf(a, b1i, acc[b][1]);
-            acc[b][1] = mfma_bf(a, b2i, acc[b][1]);
+            const uint4 a = ta[(b / NB1) * N1S + 32 * (b % NB1)];
+            acc[b][0] = mfma_bf(b1r, a, acc[b][0]);
+            acc[b][0] = mfma_bf(b2r, a, acc[b][0]);
+            acc[b][1] = mfma_bf(b1i, a, acc[b][1]);
+            acc[b][1] = mfma_bf(b2i, a, acc[b][1]);
           }
         } else if (s > 0) {
           const int pb = (s - 1) & 1;
           const int nj = (int)min((int64_t)4, m - 4 * (int64_t)(s - 1));
-          for (int jj = 0; jj < nj; ++jj) {
-            const float2 xv = Xs[(pb * NPW + jj) * 32 + (lane & 31)];
-            const float b0 = lane < 32 ? xv.x : -xv.y;
-            const float b1 = lane < 32 ? xv.y : xv.x;
-            const float* tj = Ts + ((pb * NPW + jj) * 2 + (lane >> 5)) * V + 2 * w * N1P + (lane & 31);
+          // all operands of the step first (those of tensors beyond m are
+          // read and dropped), then the MFMAs
+          float2 xv[NPW];
+          float a[NPW][BPC];
+          const float2* xs = Xs + pb * NPW * 32 + (lane & 31);
+          const float* tj = Ts + (pb * NPW * 2 + (lane >> 5)) * V + (2 / PS) * w * N1S + (lane & 31);
 #pragma unroll
-            for (int b = 0; b < BPC; ++b) {
-              const float a = tj[32 * b];
-              acc[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b0, acc[b][0], 0, 0, 0);
-              acc[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b1, acc[b][1], 0, 0, 0);
+          for (int jj = 0; jj < NPW; ++jj) {
+            xv[jj] = xs[32 * jj];
+#pragma unroll
+            for (int b = 0; b < BPC; ++b)
+              a[jj][b] = tj[2 * jj * V + (b / NB1) * N1S + 32 * (b % NB1)];
+          }
+#pragma unroll
+          for (int jj = 0; jj < NPW; ++jj) {
+            if (jj < nj) {
+              const float b0 = lane < 32 ? xv[jj].x : -xv[jj].y;
+              const float b1 = lane < 32 ? xv[jj].y : xv[jj].x;
+#pragma unroll
+              for (int b = 0; b < BPC; ++b) {
+                acc[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(b0, a[jj][b], acc[b][0], 0, 0, 0);
+                acc[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b1, a[jj][b], acc[b][1], 0, 0, 0);
+              }
             }
           }
         }
         __syncthreads();
       }
-      const int rhs = I.w * 32 + (lane & 31);
-      if (rhs < A.nrhs[I.x]) {
-        const int k = I.y;
-        const int c0 = (I.z % A.tiles2) * 8, i3 = I.z / A.tiles2;
-        float2* Y = A.out[I.x] + A.ld_out[I.x] * rhs + (int64_t)k * A.nv +
-                    (int64_t)A.n1 * ((int64_t)A.n2 * i3) + 4 * (lane >> 5);
+      // right-hand sides run along the rows of D, voxels along its lanes: a
+      // store writes 256 contiguous bytes of two columns of Y
+      const int k = I.y;
+      const int c0 = (I.z % A.tiles2) * 8, i3 = I.z / A.tiles2;
+      const int r0 = I.w * 32 + 4 * (lane >> 5), nr = A.nrhs[I.x] - r0;
+      float2* Y = A.out[I.x] + A.ld_out[I.x] * r0 + (int64_t)k * A.nv +
+                  (int64_t)A.n1 * ((int64_t)A.n2 * i3) + (lane & 31);
+      const int64_t ldy = A.ld_out[I.x];
 #pragma unroll
-        for (int b = 0; b < BPC; ++b) {
-          const int col = c0 + 2 * w + b / NB1;
-          if (col < A.n2) {
-            float2* yb = Y + (int64_t)A.n1 * col + 32 * (b % NB1);
-            const int lim = A.n1 - 32 * (b % NB1) - 4 * (lane >> 5);
+      for (int b = 0; b < BPC; ++b) {
+        const int col = c0 + (2 / PS) * w + b / NB1;
+        if (col < A.n2 && 32 * (b % NB1) + (lane & 31) < A.n1) {
+          float2* yb = Y + (int64_t)A.n1 * col + 32 * (b % NB1);
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-              if (8 * (i >> 2) + (i & 3) < lim)
-                yb[8 * (i >> 2) + (i & 3)] = make_float2(acc[b][0][i], acc[b][1][i]);
-          }
+          for (int i = 0; i < 16; ++i)
+            if (8 * (i >> 2) + (i & 3) < nr)
+              yb[(8 * (i >> 2) + (i & 3)) * ldy] = make_float2(acc[b][0][i], acc[b][1][i]);
         }
       }
     }
   } else {
-    float* tdst = Ts + (w * 2 + ((lane >> 3) & 1)) * V + (lane & 7) * N1P + 4 * (lane >> 4);
+    __builtin_amdgcn_s_setprio(2);  // a step waits for its producers
+    const int ch0 = hw * NCH;  // first 16-row chunk of this wave's share
+    float* tdst = Ts + (w * 2 + ((lane >> 3) & 1)) * V + (lane & 7) * N1S + 16 * ch0 +
+                  4 * (lane >> 4);
     for (;;) {
       const int it = next_item(A.counter, &s_item);
       if (it >= A.nitems) break;
@@ -698,35 +752,43 @@ void batch_fwd_mfma(BatchArgs A) {
       const int64_t ldx = A.ld_in[I.x];
       const int xr = min(I.w * 32 + (lane & 31), A.nrhs[I.x] - 1);
       const BTensor* bt = S.bt + (int64_t)k * S.m;
-      DecOps op;
+      DecOps<2 / PS> op;
       float ua[NCH][16];
       // Tensor j = 4s + w is decompressed in step s: its mode 2 ran in step
       // s - 1 (into Bc[s & 1]), so that step s starts mode 1 at once and runs
       // the next tensor's mode 2 alongside.  Tensor indices are clamped to
       // m - 1: loads are always issued, and only the MFMA and LDS work is
       // skipped for tensors beyond m.
-      dec_load<true>(op, bt, min((int64_t)w, m - 1), A.hcache, A.u2p, i3, c0, X, ldx, xr, lane);
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) dec_u1ops(A.u1p, op.u1p, op.r1, c, ua[c], lane);
+      const int64_t jf = min((int64_t)w, m - 1), js = min((int64_t)w + 4, m - 1);
+      const BTensor tf = bt_load(bt, jf), ts = bt_load(bt, js);
+      dec_load<true, true>(op, tf, jf, A.hcache, A.u2p, i3, c0, X, ldx, xr, hw, lane);
       float2 xcur = op.xv;
       int r1cur = op.r1;
-      if (w < m) dec_mode2(op, Bc, lane);
-      dec_load<true>(op, bt, min((int64_t)w + 4, m - 1), A.hcache, A.u2p, i3, c0, X, ldx, xr, lane);
+      const int64_t u1cur = op.u1p;
+      if (w < m) dec_mode2(op, Bc, hw, lane);
+      // the loads in the order of the loop's, so that the wait counts at its
+      // head stay exact
+      dec_load<true, true>(op, ts, js, A.hcache, A.u2p, i3, c0, X, ldx, xr, hw, lane);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) dec_u1ops<true>(A.u1p, u1cur, r1cur, ch0 + c, ua[c], lane);
+      if constexpr (PS > 1) __syncthreads();  // both row halves of Bc are written
       for (int s = 0; s <= nbat; ++s) {
         const int buf = s & 1;
         const int64_t j = 4 * (int64_t)s + w;
         const bool have = s < nbat && j < m;
         const int np1 = (r1cur + 1) >> 1;
-        if (have && lane < 32) Xs[(buf * NPW + w) * 32 + lane] = xcur;
+        const int64_t jn = min(j + 8, m - 1);
+        const BTensor tn = bt_load(bt, jn);  // record first: its latency passes under mode 2
+        if (have && hw == 0 && lane < 32) Xs[(buf * NPW + w) * 32 + lane] = xcur;
         wave_sync();
         float bb[16];
-        if (have) dec_bops(Bc + buf * NPW * 1024, bb, lane);
+        if (have) dec_bops(Bc + buf * NPW * BCN, bb, lane);
         // mode 2 of tensor j + 4 (operands in op) into the other Bc buffer
-        if (s + 1 < nbat && j + 4 < m) dec_mode2(op, Bc + (buf ^ 1) * NPW * 1024, lane);
+        if (s + 1 < nbat && j + 4 < m) dec_mode2(op, Bc + (buf ^ 1) * NPW * BCN, hw, lane);
         const float2 x4 = op.xv;
         const int r1n = op.r1;
         const int64_t u1n = op.u1p;
-        dec_load<true>(op, bt, min(j + 8, m - 1), A.hcache, A.u2p, i3, c0, X, ldx, xr, lane);
+        dec_load<true, true>(op, tn, jn, A.hcache, A.u2p, i3, c0, X, ldx, xr, hw, lane);
         float* dst = tdst + buf * NPW * 2 * V;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -737,8 +799,8 @@ void batch_fwd_mfma(BatchArgs A) {
             v4f d = {0.f, 0.f, 0.f, 0.f};
             if (have) d = chain16_n(np1, ua[c], bb);
             unsigned short* rec = reinterpret_cast<unsigned short*>(Ts) +
-                                  ((size_t)(buf * 2) * V + (lane & 7) * N1P + 16 * c +
-                                   4 * (lane >> 4)) * 8 + 4 * ((lane >> 3) & 1) + w;
+                                  ((size_t)(buf * 2) * V + (lane & 7) * N1S +
+                                   16 * (ch0 + c) + 4 * (lane >> 4)) * 8 + 4 * ((lane >> 3) & 1) + w;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const uint32_t h = bt_rne(d[r]);
@@ -749,7 +811,7 @@ void batch_fwd_mfma(BatchArgs A) {
             const v4f d = chain16_n(np1, ua[c], bb);
             *reinterpret_cast<float4*>(dst + 16 * c) = make_float4(d[0], d[1], d[2], d[3]);
           }
-          dec_u1ops(A.u1p, u1n, r1n, c, ua[c], lane);  // U1 of tensor j + 4
+          dec_u1ops<true>(A.u1p, u1n, r1n, ch0 + c, ua[c], lane);  // U1 of tensor j + 4
         }
         xcur = x4;
         r1cur = r1n;
@@ -761,23 +823,35 @@ void batch_fwd_mfma(BatchArgs A) {
 
 // Adjoint, MFMA decompression.  Item = (plan, component and slice of the
 // tiles, chunk of 32 columns, right-hand-side group); a tile is 16 NI rows
-// of i1 x 8 columns at one i3.  Per tile each wave decompresses four of the
-// 32 tensors into Tb[f][i1][jj] (row stride 33 complex, column stride
-// 16 NI + 1 rows, against LDS bank conflicts); then wave w contracts column
-// f = w: W(32 rhs x 32 columns) += Y^T conj(T) on v_mfma_f32_32x32x2f32, one
-// voxel per pair of MFMAs.  The eight waves' W are summed in a fixed order.
+// of i1 x 8 columns at one i3.  Per tile each of 16 waves decompresses two of
+// the 32 tensors into Tb[f][i1][jj] (row stride 33 complex, column stride
+// 16 NI + 1 rows, against LDS bank conflicts); then wave w contracts half of
+// column f = w / 2: W(32 rhs x 32 columns) += Y^T conj(T) on
+// v_mfma_f32_32x32x2f32, one voxel per pair of MFMAs.  The 16 waves' W are
+// summed in a fixed order.
+//
+// Decompression and contraction take turns, each bound by its matrix
+// instructions and by the latency of the loads it starts with (decompression
+// alone 7.4 ms of the case at the forward kernel, its MFMAs 3.2; contraction
+// 4.5 ms of MFMAs).  16.5 ms there with 8 waves and the operands of the next
+// slot in registers; 15.9 with 16 waves, four a SIMD, no operand prefetch; 15.3
+// with all of a tile's y loaded before the barrier and its addresses formed
+// there.  128 registers hold no prefetch: variants with one spilled and took
+// 20 to 26 ms, as did loads of only the quads in use.
 template <int NI, bool BF>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
 void batch_adj_mfma(BatchArgs A) {
-  constexpr int NW = 8, IB = 16 * NI, RS = IB + 1, TS = 33;
+  constexpr int NW = 16, IB = 16 * NI, RS = IB + 1, TS = 33, YS = 36;
   extern __shared__ float4 bsm4[];
   __shared__ int s_item;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   float2* Tb = reinterpret_cast<float2*>(bsm4);  // [8][RS][TS]
-  float* Bc = reinterpret_cast<float*>(Tb + 8 * RS * TS) + wave * 1024;
-  // y window of this wave: 8 voxels x 32 right-hand sides, row stride 33
-  float2* Ysw = reinterpret_cast<float2*>(reinterpret_cast<float*>(Tb + 8 * RS * TS) + 8 * 1024) +
-                wave * 8 * 33;
+  // Bc of this wave while it decompresses; while it contracts, its y window
+  // of 8 voxels x 32 right-hand sides, row stride 36
+  float* Bc = reinterpret_cast<float*>(Tb + 8 * RS * TS) + wave * BCN;
+  float2* Ysw = reinterpret_cast<float2*>(Bc);
+  static_assert(BCN >= 2 * 8 * YS, "y window exceeds Bc");
+  const int yc = wave >> 1, yw0 = (wave & 1) * NI;  // column, first window of its half
   const int tiles = A.nic * A.tiles2 * A.n3;
   for (;;) {
     const int it = next_item(A.counter, &s_item);
@@ -789,17 +863,15 @@ void batch_adj_mfma(BatchArgs A) {
     const int tb1 = (int)((int64_t)tiles * (slice + 1) / A.tsplit);
     const int64_t j0 = (int64_t)I.z * 32;
     const int jc = (int)min((int64_t)32, S.m - j0);
-    // y is read in windows of 8 voxels of the wave's column: lane l loads
+    // y is read in windows of 8 voxels of the wave's half column: lane l loads
     // voxel l % 8 of right-hand sides l / 8 + 8 q (q < 4), so that a load
     // instruction touches 8 half cache lines instead of 32 lines; the window
     // is transposed through LDS.  Rows >= n1, columns >= n2 and right-hand
     // sides >= nrhs are read clamped: T is zero there, and lanes beyond nrhs
     // are never stored.
-    const float2* yq[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      yq[q] = A.in[I.x] + (int64_t)k * A.nv +
-              A.ld_in[I.x] * min(I.w * 32 + (lane >> 3) + 8 * q, A.nrhs[I.x] - 1);
+    const float2* Yk = A.in[I.x] + (int64_t)k * A.nv;
+    const int64_t ldy = A.ld_in[I.x];
+    const int rb = I.w * 32, rmax = A.nrhs[I.x] - 1;
     const BTensor* bt = S.bt + (int64_t)k * S.m + j0;
     v16f acc[2];
 #pragma unroll
@@ -811,44 +883,43 @@ void batch_adj_mfma(BatchArgs A) {
       c0 = (rest % A.tiles2) * 8;
       i3 = rest / A.tiles2;
     };
-    // this wave's columns of the chunk are 4 wave + e, e < 4, valid below
-    // jc; the operands of the next slot (or of slot 0 on the next tile) are
-    // loaded while the current one is decompressed, U1 chunk by chunk as
-    // each chunk's registers retire.  Slot indices are clamped to jc - 1 so
-    // that every slot issues the same loads; invalid slots skip the work.
-    auto wload = [&](int wic0, int wc0, int wi3, int w, float2* yr) {
-      const int col = min(wc0 + wave, A.n2 - 1);
-      const int i1 = min(16 * wic0 + 8 * w + (lane & 7), A.n1 - 1);
-      const int64_t off = (int64_t)A.n1 * (col + (int64_t)A.n2 * wi3) + i1;
+    // this wave's tensors of the chunk are 2 wave + e, e < 2, valid below
+    // jc; slot indices are clamped to jc - 1 so that every slot issues the
+    // same loads, and invalid slots skip the work.  Four waves per SIMD hide
+    // the latency of the operand loads; only y is loaded a window ahead.
+    auto wload = [&](int wic0, int wc0, int wi3, int w, float2* y) {
+      // the lane is made opaque so that these addresses are formed here, not
+      // held in registers across the decompression
+      int l = lane;
+      asm volatile("" : "+v"(l));
+      const int col = min(wc0 + yc, A.n2 - 1);
+      const int i1 = min(16 * wic0 + 8 * w + (l & 7), A.n1 - 1);
+      const float2* src = Yk + (int64_t)A.n1 * (col + (int64_t)A.n2 * wi3) + i1;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) yr[q] = yq[q][off];
+      for (int q = 0; q < 4; ++q) y[q] = src[ldy * min(rb + (l >> 3) + 8 * q, rmax)];
     };
-    float2 yr[4];
-    DecOps op;
-    float ua[NI][16];
-    {
-      int ic0, c0, i3;
-      tile_pos(tb0, ic0, c0, i3);
-      wload(ic0, c0, i3, 0, yr);
-      dec_load<false>(op, bt, min(4 * wave, jc - 1), A.hcache, A.u2p, i3, c0, nullptr, 0, 0,
-                      lane);
-#pragma unroll
-      for (int ic = 0; ic < NI; ++ic) dec_u1ops(A.u1p, op.u1p, op.r1, ic0 + ic, ua[ic], lane);
-    }
+    float2 yr[NI][4];
     for (int tile = tb0; tile < tb1; ++tile) {
       int ic0, c0, i3;
       tile_pos(tile, ic0, c0, i3);
-      int nic0, nc0, ni3;
-      tile_pos(min(tile + 1, tb1 - 1), nic0, nc0, ni3);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int jj = 4 * wave + e;
+#pragma unroll 1
+      for (int e = 0; e < 2; ++e) {
+        const int jj = 2 * wave + e;
         const bool have = jj < jc;
+        DecOps<1> op;
+        const BTensor tj = bt_load(bt, min(jj, jc - 1));
+        float ua[NI][16];
+        dec_load<false, false>(op, tj, 0, A.hcache, A.u2p, i3, c0, nullptr, 0, 0, 0, lane);
         const int np1 = (op.r1 + 1) >> 1;
-        if (have) dec_mode2(op, Bc, lane);
-        const int pj = e < 3 ? min(jj + 1, jc - 1) : min(4 * wave, jc - 1);
-        const int pi3 = e < 3 ? i3 : ni3, pc0 = e < 3 ? c0 : nc0, pic0 = e < 3 ? ic0 : nic0;
-        dec_load<false>(op, bt, pj, A.hcache, A.u2p, pi3, pc0, nullptr, 0, 0, lane);
+        dec_u1ops<false>(A.u1p, op.u1p, op.r1, ic0, ua[0], lane);
+        if (have) dec_mode2(op, Bc, 0, lane);
+        if (op.r1 > 16) {
+          dec_load<false, false>(op, tj, 0, A.hcache, A.u2p, i3, c0, nullptr, 0, 0, 1, lane);
+          if (have) dec_mode2(op, Bc, 1, lane);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ic = 1; ic < NI; ++ic) dec_u1ops<false>(A.u1p, op.u1p, op.r1, ic0 + ic, ua[ic], lane);
         float bb[16];
         if (have) {
           wave_sync();
@@ -878,24 +949,26 @@ void batch_adj_mfma(BatchArgs A) {
               for (int r = 0; r < 4; ++r) dst[(16 * ic + r) * TS * 2] = d[r];
             }
           }
-          dec_u1ops(A.u1p, op.u1p, op.r1, pic0 + ic, ua[ic], lane);
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int w = 0; w < NI; ++w) wload(ic0, c0, i3, yw0 + w, yr[w]);
       __syncthreads();
-      // column f = wave of the tile, window by window
+      // half of column f = wave / 2 of the tile, window by window
       if constexpr (BF) {
         // BF16X3: K slot 8h + 2v + p of a quad of four voxels; A = y of the
         // quad (hi for lanes < 32, lo for the others), A' = (Im, -Re) of the
         // same, B = T's hi halves in both slot halves (Yh Th + Yl Th) or its
         // lo halves against y's hi (Yh Tl): Wr from A, Wi from A'.
-        const uint4* tq = reinterpret_cast<const uint4*>(Tb) + wave * (IB / 4) * 32 + (lane & 31);
+        const uint4* tq = reinterpret_cast<const uint4*>(Tb) + yc * (IB / 4) * 32 + (lane & 31);
         uint32_t* yw = reinterpret_cast<uint32_t*>(Ysw);  // [h][2 quads][32 rhs][4 words]
 #pragma unroll
-        for (int w = 0; w < IB / 8; ++w) {
+        for (int w = 0; w < NI; ++w) {
           wave_sync();
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float2 y = yr[q];
+            const float2 y = yr[w][q];
             const uint32_t hr = bt_rne(y.x), hi = bt_rne(y.y);
             const uint32_t lr = bt_rne(y.x - bt_f(hr)), li = bt_rne(y.y - bt_f(hi));
             const int i = lane & 7, rhs = (lane >> 3) + 8 * q;
@@ -904,10 +977,6 @@ void batch_adj_mfma(BatchArgs A) {
             yw[2 * 32 * 4 + o] = bt_pack(lr, li);
           }
           wave_sync();
-          if (w + 1 < IB / 8)
-            wload(ic0, c0, i3, w + 1, yr);
-          else
-            wload(nic0, nc0, ni3, 0, yr);  // first window of the next tile
 #pragma unroll
           for (int qd = 0; qd < 2; ++qd) {
             const uint4 a = reinterpret_cast<const uint4*>(yw)[((lane >> 5) * 2 + qd) * 32 + (lane & 31)];
@@ -916,7 +985,7 @@ void batch_adj_mfma(BatchArgs A) {
             a2.y = (a.y >> 16) | ((a.y ^ 0x8000u) << 16);
             a2.z = (a.z >> 16) | ((a.z ^ 0x8000u) << 16);
             a2.w = (a.w >> 16) | ((a.w ^ 0x8000u) << 16);
-            const int quad = 2 * w + qd;
+            const int quad = 2 * (yw0 + w) + qd;
             const uint4 b1 = tq[quad * 32];
             const uint4 b2 = lane < 32 ? tq[2 * IB * 32 + quad * 32] : make_uint4(0u, 0u, 0u, 0u);
             acc[0] = mfma_bf(a, b1, acc[0]);
@@ -926,21 +995,17 @@ void batch_adj_mfma(BatchArgs A) {
           }
         }
       } else {
-      const float2* tc = Tb + wave * RS * TS + (lane & 31);
+      const float2* tc = Tb + yc * RS * TS + (lane & 31);
 #pragma unroll
-      for (int w = 0; w < IB / 8; ++w) {
+      for (int w = 0; w < NI; ++w) {
         wave_sync();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) Ysw[(lane & 7) * 33 + (lane >> 3) + 8 * q] = yr[q];
+        for (int q = 0; q < 4; ++q) Ysw[(lane & 7) * YS + (lane >> 3) + 8 * q] = yr[w][q];
         wave_sync();
-        if (w + 1 < IB / 8)
-          wload(ic0, c0, i3, w + 1, yr);
-        else
-          wload(nic0, nc0, ni3, 0, yr);  // first window of the next tile
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float2 yv = Ysw[i * 33 + (lane & 31)];
-          const float2 tb = tc[(8 * w + i) * TS];
+          const float2 yv = Ysw[i * YS + (lane & 31)];
+          const float2 tb = tc[(8 * (yw0 + w) + i) * TS];
           const float bv = lane < 32 ? tb.x : -tb.y;
           const float a0 = lane < 32 ? yv.x : -yv.y;
           const float a1 = lane < 32 ? yv.y : yv.x;
@@ -951,35 +1016,32 @@ void batch_adj_mfma(BatchArgs A) {
       }
       __syncthreads();
     }
-    // sum the eight waves' W in a fixed order
+    // sum the 16 waves' W in a fixed order, wave i the rows of register i
     float* red = reinterpret_cast<float*>(Tb);
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) red[((wave * 2 + mb) * 16 + i) * 64 + lane] = acc[mb][i];
     __syncthreads();
-    if (wave == 0) {
+    {
       float2* blk = A.partial + (int64_t)it * 1024;
+      float wr = 0.f, wi = 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float wr = 0.f, wi = 0.f;
-        for (int w = 0; w < NW; ++w) {
-          wr += red[((w * 2 + 0) * 16 + i) * 64 + lane];
-          wi += red[((w * 2 + 1) * 16 + i) * 64 + lane];
-        }
-        const int rl = 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        blk[rl * 32 + (lane & 31)] = make_float2(wr, wi);
+      for (int w = 0; w < NW; ++w) {
+        wr += red[((w * 2 + 0) * 16 + wave) * 64 + lane];
+        wi += red[((w * 2 + 1) * 16 + wave) * 64 + lane];
       }
+      const int rl = 8 * (wave >> 2) + 4 * (lane >> 5) + (wave & 3);
+      blk[rl * 32 + (lane & 31)] = make_float2(wr, wi);
     }
   }
 }
 
 size_t batch_mfma_lds_bytes(int op, int nb) {
-  if (op == 0) return sizeof(float) * (2 * 4 * 2 * (8 * 32 * nb) + 2 * 4 * 64 + 2 * 4 * 1024);
-  // Tb, then Bc, then the y windows; the final reduction reuses the start
+  if (op == 0) return sizeof(float) * (2 * 4 * 2 * 8 * (32 * nb + 4) + 2 * 4 * 64 + 2 * 4 * BCN);
+  // Tb, then one Bc per wave; the final reduction reuses the start
   const size_t tb = sizeof(float2) * 8 * (16 * nb + 1) * 33;
-  const size_t all = tb + sizeof(float) * 8 * 1024 + sizeof(float2) * 8 * 8 * 33;
-  return std::max(all, sizeof(float) * 8 * 2 * 16 * 64);
+  return std::max(tb + sizeof(float) * 16 * BCN, sizeof(float) * 16 * 2 * 16 * 64);
 }
 
 size_t batch_lds_bytes(int op, int ncol, int n1p32, int r1max, int r2max) {
@@ -1029,6 +1091,7 @@ struct tv_batch_s {
   int r1max = 1, r2max = 1, r3max = 1;
   int nitems = 0;
   int grid_blocks = 0;
+  int threads = 256;
   int per_cu = 1;           // persistent workgroups per compute unit
   size_t lds = 0;
   std::vector<int64_t> m;
@@ -1143,11 +1206,11 @@ tv_status tv_batch_create(int32_t nplans, const tv_plan* plans, int32_t op, cons
       for (int c = 0; c < nplans; ++c) bf = bf && plans[c]->precision == TV_PREC_BF16X3;
       b->bf = bf;
       if (bf)
-        b->fn = nb1 == 1 ? batch_fwd_mfma<1, true> : nb1 == 2 ? batch_fwd_mfma<2, true>
-                                                              : batch_fwd_mfma<3, true>;
+        b->fn = nb1 == 1 ? batch_fwd_mfma<1, true, 1> : nb1 == 2 ? batch_fwd_mfma<2, true, 2>
+                                                              : batch_fwd_mfma<3, true, 2>;
       else
-        b->fn = nb1 == 1 ? batch_fwd_mfma<1, false> : nb1 == 2 ? batch_fwd_mfma<2, false>
-                                                               : batch_fwd_mfma<3, false>;
+        b->fn = nb1 == 1 ? batch_fwd_mfma<1, false, 1> : nb1 == 2 ? batch_fwd_mfma<2, false, 2>
+                                                               : batch_fwd_mfma<3, false, 2>;
     } else {
       const int ni = std::min(3, (g.n1 + 15) / 16);
       b->bpw = ni;
@@ -1186,7 +1249,7 @@ tv_status tv_batch_create(int32_t nplans, const tv_plan* plans, int32_t op, cons
     delete b;
     return set_error(TV_ERR_NOT_SUPPORTED, "no batched kernel for these sizes and ranks");
   }
-  const int threads = b->mfma ? 512 : 256;
+  b->threads = !b->mfma ? 256 : op == 1 || nb1 > 1 ? 1024 : 512;
   b->tiles2 = (g.n2 + b->ncol - 1) / b->ncol;
   // work items, longest first (most tensors per item); the adjoint splits
   // the voxel tiles of each (plan, component, chunk) into tsplit slices so
@@ -1275,16 +1338,19 @@ tv_status tv_batch_create(int32_t nplans, const tv_plan* plans, int32_t op, cons
                     u1p[u1o + (((size_t)ic * nq1 + q) * 64 + l) * 4 + i] = (float)
                         P->u1[2 * (P->u1_off[t] + i1 + (size_t)g.n1 * a) + ((l >> 4) & 1)];
                 }
-          // block (cg, q), lane l, step t: Re/Im (part ^ s) of U2[8 cg + l%8][2t + l/32]
+          // block (cg, q), lane l, step t: Re/Im (part ^ s) of U2[8 cg + l%8][2t + l/32],
+          // -U2i at part 0, s = 1
           for (int cg = 0; cg < ncg; ++cg)
             for (int q = 0; q < nq2; ++q)
               for (int l = 0; l < 64; ++l)
                 for (int i = 0; i < 4; ++i) {
                   const int i2 = 8 * cg + (l & 7), bb = 2 * (4 * q + i) + (l >> 5);
                   const int comp = ((l >> 3) ^ (l >> 4)) & 1;
-                  if (i2 < g.n2 && bb < r2)
-                    u2p[u2o + (((size_t)cg * nq2 + q) * 64 + l) * 4 + i] =
-                        (float)P->u2[2 * (P->u2_off[t] + i2 + (size_t)g.n2 * bb) + comp];
+                  const bool neg = ((l >> 3) & 1) == 0 && ((l >> 4) & 1) == 1;
+                  if (i2 < g.n2 && bb < r2) {
+                    const float v = (float)P->u2[2 * (P->u2_off[t] + i2 + (size_t)g.n2 * bb) + comp];
+                    u2p[u2o + (((size_t)cg * nq2 + q) * 64 + l) * 4 + i] = neg ? -v : v;
+                  }
                 }
           u1o += (size_t)b->nch * nq1 * 256;
           u2o += (size_t)ncg * nq2 * 256;
@@ -1321,7 +1387,7 @@ tv_status tv_batch_create(int32_t nplans, const tv_plan* plans, int32_t op, cons
   if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)b->fn, threads, b->lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)b->fn, b->threads, b->lds);
   if (e != hipSuccess) {
     batch_free(b);
     return hip_error(e, "tv_batch_create");
@@ -1454,12 +1520,12 @@ tv_status tv_batch_run(tv_batch b, const void* const* in, const int64_t* ld_in, 
     e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "mode-3 kernel launch");
   }
-  hipLaunchKernelGGL(b->fn, dim3((unsigned)b->grid_blocks), dim3(b->mfma ? 512 : 256), b->lds,
-                     st, A);
+  hipLaunchKernelGGL(b->fn, dim3((unsigned)b->grid_blocks), dim3((unsigned)b->threads), b->lds, st,
+                     A);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "batched kernel launch");
   if (b->op == 1) {
-    hipLaunchKernelGGL(batch_adj_reduce, dim3((unsigned)b->nred), dim3(256), 0, st, A,
+    hipLaunchKernelGGL(batch_adj_reduce, dim3((unsigned)b->nred, 16), dim3(1024), 0, st, A,
                        b->d_red_list, b->d_red_out, b->nper);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "batched reduction launch");
@@ -1505,7 +1571,7 @@ tv_status tv_batch_autotune(int32_t nplans, const tv_plan* plans, int32_t op,
   }
   const tv_grid g0 = plans[0]->grid;
   char key[256];
-  snprintf(key, sizeof key, "b1|%s|%dx%dx%d|q%d|n%d|h%016llx|op%d", device_arch().c_str(), g0.n1,
+  snprintf(key, sizeof key, "b2|%s|%dx%dx%d|q%d|n%d|h%016llx|op%d", device_arch().c_str(), g0.n1,
            g0.n2, g0.n3, g0.q, nplans, (unsigned long long)h, op);
   auto cache = read_tune_cache(cache_path);
   auto it = cache.find(key);
