@@ -1571,7 +1571,7 @@ tv_status tv_batch_autotune(int32_t nplans, const tv_plan* plans, int32_t op,
   }
   const tv_grid g0 = plans[0]->grid;
   char key[256];
-  snprintf(key, sizeof key, "b2|%s|%dx%dx%d|q%d|n%d|h%016llx|op%d", device_arch().c_str(), g0.n1,
+  snprintf(key, sizeof key, "b1|%s|%dx%dx%d|q%d|n%d|h%016llx|op%d", device_arch().c_str(), g0.n1,
            g0.n2, g0.n3, g0.q, nplans, (unsigned long long)h, op);
   auto cache = read_tune_cache(cache_path);
   auto it = cache.find(key);
