@@ -76,9 +76,20 @@ def kernel_label(family, d):
     if family == 1:
         return "tv::ws_fused"
     if d == 0:
-        return "tv_matvec call: dtg_decomp_kernel + dtg_gemm_kernel"
-    return ("tv_rmatvec call: dtg_decomp_kernel + dtg_ypack_kernel + dtg_colgemm_kernel + "
+        return "tv_matvec call: dtg_decomp_kernel + dtg_split_gemm"
+    return ("tv_rmatvec call: dtg_decomp_kernel + dtg_ypack_kernel + dtg_split_gemm + "
             "dtg_colgemm_reduce_kernel")
+
+
+def mfma_peak(family, fp32):
+    """Matrix peak of a product call in algorithmic TFLOP/s: BF16X3 executes
+    three BF16 products per algorithmic one; the FP32 decompress-then-GEMM
+    path six (an exact split into three planes), the other FP32 paths run on
+    the FP32 matrix instructions."""
+    if not fp32:
+        return PEAK_BF16_MFMA / 3.0
+    return PEAK_BF16_MFMA / 6.0 if family == 2 else PEAK_FP32_MFMA
+
 
 def measured_traffic(workload: str, precision: str, direction: str, info=None):
     """HBM bytes per call from the committed counter profile, or None when
@@ -292,8 +303,7 @@ def main(argv=None):
     kname = kernel_label(info.kernel[d], d)
     pname = "fp32" if prec == lib.TV_PREC_FP32 else "bf16x3"
     ach = tf_a if dom == "adjoint" else tf_f
-    # the BF16 split executes 3 MFMA products per algorithmic one
-    peak = PEAK_FP32_MFMA if prec == lib.TV_PREC_FP32 else PEAK_BF16_MFMA / 3.0
+    peak = mfma_peak(info.kernel[d], prec == lib.TV_PREC_FP32)
     mode1 = 8.0 * wl.grid.n1 * wl.grid.n2 * wl.grid.n3 * info.sum_r1
     out = {
         "metric": "compressed VSIE matvecs/s (Zx and Z^H y), TFLOP/s and % MFMA peak",
@@ -534,7 +544,7 @@ def bench_aca(args):
     info = plan.info
     kname = kernel_label(info.kernel[d], d)
     ach = tf_a if dom == "adjoint" else tf_f
-    peak = PEAK_FP32_MFMA if prec == lib.TV_PREC_FP32 else PEAK_BF16_MFMA / 3.0
+    peak = mfma_peak(info.kernel[d], prec == lib.TV_PREC_FP32)
     mode1 = 8.0 * wl.grid.n1 * wl.grid.n2 * wl.grid.n3 * info.sum_r1
     out = {
         "metric": "ACA+Tucker coupling-matrix products/s (U (V^* x) and V (U^* y))",
