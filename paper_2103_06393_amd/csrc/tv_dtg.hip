@@ -519,9 +519,8 @@ void dtg_default(tv_plan_s* p) {
                                  (int64_t)g.n2 * s3 / (3 * DTG_KC)), 32);
   // FP32 chains of at most 256 columns (512 where the partials of Z would pass
   // 2 GiB): the fused adjoint sums little in FP32 before its FP64 sum
-  // (81x44x108 x 250, error against 64 bits, mean of three draws: fused 2.9e-7,
-  // chains of 256 columns 3.1e-7 in 2.60 ms, of 128 3.0e-7 in 2.95 ms; one
-  // draw: 2400 columns 4.3e-7, 512 3.3e-7, 256 2.9e-7)
+  // (81x44x108 x 250: error against 64 bits 2.7e-7 there, 2.4e-7 with chains
+  // of 256 columns, which take 2.57 ms, 2.95 with 128)
   if (dtg_planes(p) == 3) {
     const int64_t cols = (int64_t)g.n2 * s3, z = p->dtg_rows * g.n1 * (int64_t)sizeof(float2);
     const int64_t chain = z * nslab * ((cols + 255) / 256) <= (int64_t)2 << 30 ? 256 : 512;

@@ -16,7 +16,11 @@
 //     to FP32 after every 8 products (measured: K = 16 has the error of two
 //     roundings), so six of them per 16 k-steps on the running sum would round
 //     it 12 times; a chunk is summed from zero instead and then added, one
-//     rounding of the running sum per 16 k-steps (CHUNK_SUM).
+//     rounding of the running sum per 16 k-steps (CHUNK_SUM).  The MFMA cuts
+//     the bits of smaller addends towards minus infinity, a bias that adds up
+//     where the terms' signs are random and U1 is smooth; odd chunks form the
+//     negated products and are subtracted, which cancels it (adjoint of 512
+//     dipole columns on 128^3, random y: error 3.2e-6 without, 4.9e-7 with).
 //   NS = 2 (BF16X3 plans): hh, hl, lh.
 //
 // One LDS stage is a chunk of 16 real k-steps (8 stacked rows, or 8 columns,
@@ -39,8 +43,8 @@
 // the FP32 MFMA GEMM (v_mfma_f32_32x32x2f32, 1/16 of the bf16 rate) that this
 // one replaced: 256^3 x 2048 columns, adjoint GEMM 56.4 -> 35.2 ms (203
 // TFLOP/s; 31.2 ms without CHUNK_SUM), relative error against 64 bits 1.2e-6
-// -> 7.7e-7 (1.5e-6 without CHUNK_SUM: why it is kept); 205 x 109 x 270 x 287
-// forward GEMM 7.5 -> 4.3 ms, error 1.7e-6 -> 5.1e-7; BF16X3 256^3 x 256
+// -> 4.4e-7 (1.5e-6 without CHUNK_SUM, 7.7e-7 without the negated chunks); 205 x 109 x 270 x 287
+// forward GEMM 7.5 -> 4.3 ms, error 1.8e-6 -> 4.9e-7; BF16X3 256^3 x 256
 // forward 3.0 -> 2.3, adjoint 3.1 -> 2.4 ms.
 #pragma once
 
@@ -228,6 +232,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
       for (int e = 0; e < 4; ++e) {
         float2 v = rb[e];
         if (tail && k0 + e >= kext) v = make_float2(0.f, 0.f);
+        if (CHUNK_SUM && buf) v = make_float2(-v.x, -v.y);  // odd chunks, see step
         bf_split<NS>(v.x, v.y, wd[e]);
       }
 #pragma unroll
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
       for (int j = 0; j < NBW; ++j) {
         if (CHUNK_SUM) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += t[j][r];
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += buf ? -t[j][r] : t[j][r];
         } else {
           acc[i][j] = t[j];
         }
