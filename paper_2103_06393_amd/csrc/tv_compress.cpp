@@ -21,8 +21,8 @@
 
 namespace tv {
 tv_status launch_gram(const double2* A, int ntens, int n1, int n2, int n3, int nmax, double2* S,
-                      double2* P, hipStream_t st);
-size_t gram_partial_count(int ntens, int nmax);
+                      double2* P, size_t npart, hipStream_t st);
+size_t gram_partial_count(int ntens, int nmax, bool least);
 tv_status launch_jacobi(const double2* S, int nmat, int n, int64_t stride, double* W,
                         int64_t wstride, double2* V, int64_t vstride, hipStream_t st);
 tv_status launch_proj(const double2* A, int ntens, int n1, int n2, int n3, const double2* u1,
@@ -57,16 +57,18 @@ struct DevScratch {
   }
 };
 
-// Upper bound of the scratch of one append call of T tensors: Gram
-// matrices (and their partial tiles when the columns are split), eigenpairs
-// (and the subspace solver's work arrays for modes longer than 64), factors
-// at the largest rank a mode can keep, and the partial projections and cores
-// of the core computation.  The call carves some of these as one region (one
-// copy each way), which never needs more than the separately aligned pieces.
-size_t compress_scratch_bytes(const tv_plan_s* p, int T) {
+static int longest_mode(const tv_grid& g) { return std::max(g.n1, std::max(g.n2, g.n3)); }
+
+// Upper bound of the scratch of one append call of T tensors with npart
+// double2 of partial Gram tiles: Gram matrices, eigenpairs (and the subspace
+// solver's work arrays for modes longer than 64), factors at the largest rank
+// a mode can keep, and the partial projections and cores of the core
+// computation.  The call carves some of these as one region (one copy each
+// way), which never needs more than the separately aligned pieces.
+static size_t scratch_bytes(const tv_plan_s* p, int T, size_t npart) {
   const tv_grid& g = p->grid;
   const int dims[3] = {g.n1, g.n2, g.n3};
-  const int nmax = std::max(g.n1, std::max(g.n2, g.n3));
+  const int nmax = longest_mode(g);
   int rmax[3];
   for (int d = 0; d < 3; ++d) {
     int r = std::min(dims[d], std::min(64, TV_MAX_RANK));
@@ -79,7 +81,7 @@ size_t compress_scratch_bytes(const tv_plan_s* p, int T) {
   int64_t* zi;
   int* zk;
   ds.alloc(&z2, (size_t)3 * T * nmax * nmax);
-  ds.alloc(&z2, gram_partial_count(T, nmax));
+  ds.alloc(&z2, npart);
   for (int d = 0; d < 3; ++d) {
     const int n = dims[d], L = n <= 64 ? n : 64;
     ds.alloc(&z2, (size_t)T * n * L);
@@ -96,6 +98,23 @@ size_t compress_scratch_bytes(const tv_plan_s* p, int T) {
   ds.alloc(&zi, (size_t)4 * T);
   ds.alloc(&zk, (size_t)3 * T);
   return (ds.off + 255) & ~(size_t)255;
+}
+
+// The least scratch a call of T tensors runs with.
+static size_t least_scratch_bytes(const tv_plan_s* p, int T) {
+  return scratch_bytes(p, T, gram_partial_count(T, longest_mode(p->grid), true));
+}
+
+// Scratch asked for a call of T tensors: with the partial Gram tiles it runs
+// fastest with, and never less than a call of fewer tensors (the last one of a
+// plan compressed in equal chunks) runs with.
+size_t compress_scratch_bytes(const tv_plan_s* p, int T) {
+  const int nmax = longest_mode(p->grid);
+  size_t need = scratch_bytes(p, T, gram_partial_count(T, nmax, false));
+  // from 512 workgroups on the least scratch has no partial tiles and grows with T
+  const int tiles = (nmax + 63) / 64, per = 3 * (tiles * (tiles + 1) / 2);
+  for (int t = std::min(T, 511 / per); t >= 1; --t) need = std::max(need, least_scratch_bytes(p, t));
+  return need;
 }
 
 // Rank of one mode from its leading eigenvalues lam (descending, L of the
@@ -215,7 +234,7 @@ tv_status compress_append_staged(tv_plan p, const void* cols, int64_t ncols, voi
     return set_error(TV_ERR_NOT_SUPPORTED, "at most 65535 tensors per append call");
   const tv_grid& g = p->grid;
   const int dims[3] = {g.n1, g.n2, g.n3};
-  const int nmax = std::max(g.n1, std::max(g.n2, g.n3));
+  const int nmax = longest_mode(g);
   const int64_t nv = (int64_t)g.n1 * g.n2 * g.n3;
   const int T = (int)(ncols * g.q);
   const double2* A = (const double2*)cols;
@@ -233,7 +252,7 @@ tv_status compress_append_staged(tv_plan p, const void* cols, int64_t ncols, voi
     stage_off = (stage_off + n * sizeof(double2) + 255) & ~(size_t)255;
     return q;
   };
-  const size_t need = compress_scratch_bytes(p, T);
+  const size_t need = least_scratch_bytes(p, T);
   if (!ws || ws_bytes < need) {
     char buf[128];
     snprintf(buf, sizeof buf, "compression workspace of %zu bytes needed, %zu given", need,
@@ -251,10 +270,13 @@ tv_status compress_append_staged(tv_plan p, const void* cols, int64_t ncols, voi
   //    64 pairs by subspace iteration otherwise
   const int64_t mat = (int64_t)nmax * nmax;
   double2* dS;
-  double2* dP;  // partial Gram tiles of calls with few tensors
+  double2* dP;  // partial Gram tiles of calls with few tensors, as far as there is room
+  size_t npart = gram_partial_count(T, nmax, false);
+  const size_t rest = scratch_bytes(p, T, 0);
+  npart = std::min(npart, ws_bytes > rest ? (ws_bytes - rest) / sizeof(double2) : 0);
   if ((s = ds.alloc(&dS, (size_t)3 * T * mat)) != TV_OK) return s;
-  if ((s = ds.alloc(&dP, gram_partial_count(T, nmax))) != TV_OK) return s;
-  if ((s = launch_gram(A, T, g.n1, g.n2, g.n3, nmax, dS, dP, st)) != TV_OK) return s;
+  if ((s = ds.alloc(&dP, npart)) != TV_OK) return s;
+  if ((s = launch_gram(A, T, g.n1, g.n2, g.n3, nmax, dS, dP, npart, st)) != TV_OK) return s;
   int L[3];
   // the three modes' eigenproblems: subspace preparation for the long modes,
   // then one Jacobi launch over every mode's matrices (n x n directly for

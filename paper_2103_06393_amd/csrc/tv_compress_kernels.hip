@@ -510,25 +510,31 @@ static tv_status last(const char* what) {
 // between 512 and 2048 workgroups, three or fewer per CU with the off-diagonal
 // tiles last, so that about 4096 do (32 columns of 128^3, 864 workgroups: 9.6
 // -> 8.2 ms; three waves per SIMD instead of two then took it to 7.6).
-int gram_splits(int ntens, int nmax) {
+static int64_t gram_tiles(int ntens, int nmax) {
   const int tiles = (nmax + 63) / 64;
-  const int64_t base = (int64_t)ntens * 3 * (tiles * (tiles + 1) / 2);
-  if (base >= 2048) return 1;
+  return (int64_t)ntens * 3 * (tiles * (tiles + 1) / 2);
+}
+static int gram_splits(int64_t base, bool least) {
+  if (base >= (least ? 512 : 2048)) return 1;
   return (int)std::min<int64_t>(64, ((base < 512 ? 1024 : 4096) + base - 1) / base);
 }
 
-size_t gram_partial_count(int ntens, int nmax) {
-  const int s = gram_splits(ntens, nmax);
-  const int tiles = (nmax + 63) / 64;
-  return s > 1 ? (size_t)s * ntens * 3 * (tiles * (tiles + 1) / 2) * 4096 : 0;
+// Partial tiles (double2 units): what the products are given when there is
+// room, or the least they are run with.  The second form is 0 from 512
+// workgroups on: those fill the chip unsplit, and a workspace sized for more
+// tensors need not hold the partial tiles that fewer would like.
+size_t gram_partial_count(int ntens, int nmax, bool least) {
+  const int64_t base = gram_tiles(ntens, nmax);
+  const int s = gram_splits(base, least);
+  return s > 1 ? (size_t)s * base * 4096 : 0;
 }
 
+// P: room for npart (double2 units) of partial tiles
 tv_status launch_gram(const double2* A, int ntens, int n1, int n2, int n3, int nmax, double2* S,
-                      double2* P, hipStream_t st) {
-  const int tiles = (nmax + 63) / 64;
-  const int64_t base = (int64_t)ntens * 3 * (tiles * (tiles + 1) / 2);
-  const int ns = gram_splits(ntens, nmax);
-  if (ns > 1 && !P) return set_error(TV_ERR_INVALID_ARG, "gram: partial buffer missing");
+                      double2* P, size_t npart, hipStream_t st) {
+  const int64_t base = gram_tiles(ntens, nmax);
+  const int ns = (int)std::max<int64_t>(
+      1, std::min<int64_t>(gram_splits(base, false), P ? (int64_t)npart / (base * 4096) : 0));
   hipLaunchKernelGGL(gram_kernel, dim3((unsigned)(base * ns)), dim3(256), 0, st, A, ntens, n1,
                      n2, n3, nmax, ns, S, P);
   tv_status s = last("gram_kernel");

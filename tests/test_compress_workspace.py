@@ -1,0 +1,56 @@
+"""The workspace of an append call covers every later call of fewer columns: a
+plan is compressed in equal chunks with one workspace, the last chunk shorter.
+The partial tiles of the Gram products, which smaller calls use and larger ones
+do not, take what room there is."""
+import numpy as np
+import pytest
+
+CHUNKS = [      # grid, rank cap, full chunk, last chunk
+    ((32, 32, 32), 12, 256, 200),
+    ((64, 64, 64), 12, 256, 200),
+    ((128, 128, 128), 32, 76, 75),
+    ((256, 256, 256), 4, 32, 22),
+    ((96, 40, 50), 8, 60, 56),
+]
+
+
+@pytest.mark.parametrize("dims,cap,full,rest", CHUNKS)
+def test_workspace_covers_shorter_chunks(dims, cap, full, rest):
+    from paper_2103_06393_amd import lib
+    h = lib.tv_compress_begin(lib.make_grid(*dims, 3, full + rest), 1e-3, 1, cap)
+    try:
+        # the append validates before any device work: with a workspace that is
+        # large enough it gets as far as the 256-byte alignment, else it is
+        # refused as too small
+        given = lib.tv_compress_workspace_bytes(h, full)
+        for n in {1, 2, rest, full - 1, full} | set(range(1, full, 13)):
+            with pytest.raises(lib.TuckVsieError) as e:
+                lib.tv_compress_append(h, 1 << 20, n, (1 << 24) + 16, given, None)
+            assert e.value.status == -1 and "aligned" in str(e.value), (n, str(e.value))
+    finally:
+        lib.tv_plan_destroy(h)
+
+
+@pytest.mark.gpu
+def test_shorter_last_chunk_compresses_as_one(gpu_lib):
+    """456 columns of 32^3 in chunks of 256 + 200 against one call: the same
+    FP64 Gram products, summed over other column ranges."""
+    import workloads
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    print("compress 32^3, 456 columns, chunks of 256", flush=True)
+    m = 456
+    wl = workloads.make("c1")
+    ang = np.linspace(0.0, 2.0 * np.pi, m, endpoint=False)
+    r = np.linalg.norm(wl.pos[0][:2])
+    pos = np.stack([r * np.cos(ang), r * np.sin(ang), np.zeros(m)], axis=1)
+    ori = np.stack([-np.sin(ang), np.cos(ang), np.zeros(m)], axis=1)
+    plans = [TuckerPlan.compress_dipoles(wl.grid.dims, wl.grid.h, wl.k0, 0, pos, ori, 1e-4,
+                                         rank_cap=12, chunk=c) for c in (256, m)]
+    a, b = (P.export_factors() for P in plans)
+    assert np.array_equal(a[0], b[0])
+    import torch
+    x = torch.randn(m, dtype=torch.complex64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(1))
+    ya, yb = (P.matvec(x) for P in plans)
+    assert float((ya - yb).norm() / yb.norm()) < 1e-5
