@@ -185,8 +185,10 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
 /* Launch configuration of one direction of a plan's products (what the
  * autotuner chooses; set-up call, not thread-safe against concurrent
  * products on the same plan).  A new plan starts on the path that a rule on
- * its size picks: path 1, in slabs of at most 4 GiB, from about 0.4 GFLOP (for
- * tv_rmatvec only where tv_rmatvec_noalloc can run it too).
+ * its size picks, in a workspace of at most 4 GiB: path 1 from 0.3 GFLOP of
+ * mode 1 (8 n1 n2 n3 sum r1) forward, and 0.4 adjoint, or 1.2 below 256 stacked
+ * rows per component (for tv_rmatvec only where tv_rmatvec_noalloc can run it
+ * too; tv_aca_rmatvec goes by the size alone).
  *   path 0: the fused kernels (Algorithms 1/2 with decompression inside the
  *     mode-1 product): tile_t2 = i2 extent of a workgroup tile (0: the tile
  *     covering the fewest columns), splits = column-range splits (split-K
@@ -203,7 +205,8 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
  *     GEMM per slab over the slab's columns (tiles of 64 gemm_nbw stacked
  *     rows, splits 1..64 column splits, gemm_order 0:
  *     workgroups sharing B rows adjacent, 1: sharing y columns adjacent),
- *     one FP32 partial per slab and split, then x'_j = sum conj(U1_j) Z_k
+ *     one FP32 partial per slab and split (of as many slabs at a time as
+ *     take 2 GiB), then x'_j = sum conj(U1_j) Z_k
  *     with the partials summed in FP64 (Algorithms 1 and 2, Sec. III.B).
  *     row_cap on path 1: 0 (the plan's GEMM tile along the voxel rows) or
  *     8 (BF16X3 plans with 128 < n1 <= 256, with gemm_nbw 2: one workgroup

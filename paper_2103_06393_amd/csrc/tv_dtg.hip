@@ -309,6 +309,8 @@ __global__ void dtg_ypack_kernel(YPackParams P) {
 // x'_j = sum_k sum_{a < r1} sum_i1 conj(U1_j[i1][a]) sum_s Z_s[row a][i1]
 // over the partials s of every slab and split, in FP64 and a fixed order: one
 // workgroup per column j, its 16 waves share the rows (k, a), a lane per i1.
+// Where not all slabs' partials are held at once, a launch per group of slabs
+// carries the FP64 sum of column j on in acc.
 // Bound by the reads of Z (and by their latency where m is below the CUs:
 // eight partials' loads are in flight a lane).  128^3, q = 12, 128 columns, 16
 // partials (214 MB): 690 -> 57 us against
@@ -319,9 +321,11 @@ struct ColReduceParams {
   const float2* u1t;
   const float2* z;
   float2* x;
+  double2* acc;             // null: all partials are in this launch
   int64_t brow[DTG_MAXQ];
   int64_t zsplit, m;
   int q, S, n1;
+  bool first, last;         // group of slabs
 };
 constexpr int RED_T = 1024;
 __global__ __launch_bounds__(RED_T) void dtg_colgemm_reduce_kernel(ColReduceParams P) {
@@ -374,6 +378,16 @@ __global__ __launch_bounds__(RED_T) void dtg_colgemm_reduce_kernel(ColReducePara
     for (int w = 1; w < RED_T / 64; ++w) {
       sr += red[0][w];
       si += red[1][w];
+    }
+    if (P.acc) {
+      if (!P.first) {
+        sr += P.acc[j].x;
+        si += P.acc[j].y;
+      }
+      if (!P.last) {
+        P.acc[j] = make_double2(sr, si);
+        return;
+      }
     }
     P.x[j] = make_float2((float)sr, (float)si);
   }
@@ -492,11 +506,17 @@ bool dtg_supported(const tv_plan_s* p) { return p->dtg_packed && p->grid.q <= DT
 // chunks each at least (64^3 x 256: 317 -> 165, best of all splits and tiles
 // 163).  Adjoint tiles of 256 stacked rows, or 128 where those pad a seventh
 // less or the rows fit one (two workgroups then share a CU), column splits
-// towards a full chip, 48 columns each at least, 32 at most.  Slabs of at most
-// 4 GiB.
+// towards a full chip, 48 columns each at least, 32 at most.
+// FP32 plans' adjoint: FP32 chains of at most 256 columns (512 where all
+// partials of Z would pass 2 GiB at that), since the fused adjoint sums little
+// in FP32 before its FP64 sum (81x44x108 x 250: error against 64 bits 2.7e-7
+// there, 2.4e-7 with chains of 256 columns, which take 2.57 ms, 2.95 with 128).
+// Slabs as high as that leaves 64 splits and the whole workspace 4 GiB; a plan
+// whose single i3 needs more stays on the fused kernels.
 void dtg_default(tv_plan_s* p) {
   if (!dtg_supported(p)) return;
   const tv_grid& g = p->grid;
+  constexpr size_t bound = (size_t)4 << 30;
   const double gflop = 8e-9 * (double)p->sum_r1 * g.n1 * g.n2 * g.n3;
   const int64_t rows_k = p->dtg_rows / g.q;
   const auto pow2 = [](int64_t n, int64_t most) {
@@ -504,32 +524,33 @@ void dtg_default(tv_plan_s* p) {
     while (2 * s <= std::min(n, most)) s *= 2;
     return s;
   };
-  const int64_t per_i3 = std::max<int64_t>(1, p->dtg_rows * g.n2 * (int64_t)sizeof(float2));
-  const int64_t fit = std::max<int64_t>(1, ((int64_t)4 << 30) / per_i3);
-  const int64_t nslab = (g.n3 + fit - 1) / fit;
-  const int s3 = (int)((g.n3 + nslab - 1) / nslab);
-  p->dtg_s3 = p->dtg_s3_a = s3;
+  bool fits[2] = {false, false};
   p->dtg_nbw = 4;
-  p->dtg_split = pow2(std::min(256 / std::max<int64_t>(1, dtg_launch_tiles(p, s3, 4)),
-                               rows_k / 8 / 8), 16);
+  for (int nslab = 1; nslab <= g.n3 && !fits[0]; ++nslab) {
+    p->dtg_s3 = (g.n3 + nslab - 1) / nslab;
+    p->dtg_split = pow2(std::min(256 / std::max<int64_t>(1, dtg_launch_tiles(p, p->dtg_s3, 4)),
+                                 rows_k / 8 / 8), 16);
+    fits[0] = dtg_workspace_bytes(p, 0) <= bound;
+  }
   const int64_t t4 = dtg_colgemm_tiles(p, 4), t2 = dtg_colgemm_tiles(p, 2);
   p->dtg_nbw_a = rows_k <= 256 || 16 * t4 > 9 * t2 ? 2 : 4;
   const int64_t tiles = p->dtg_nbw_a == 4 ? t4 : t2, slots = p->dtg_nbw_a == 4 ? 256 : 512;
-  p->dtg_split_a = pow2(std::min(slots / std::max<int64_t>(1, tiles),
-                                 (int64_t)g.n2 * s3 / (3 * DTG_KC)), 32);
-  // FP32 chains of at most 256 columns (512 where the partials of Z would pass
-  // 2 GiB): the fused adjoint sums little in FP32 before its FP64 sum
-  // (81x44x108 x 250: error against 64 bits 2.7e-7 there, 2.4e-7 with chains
-  // of 256 columns, which take 2.57 ms, 2.95 with 128)
-  if (dtg_planes(p) == 3) {
-    const int64_t cols = (int64_t)g.n2 * s3, z = p->dtg_rows * g.n1 * (int64_t)sizeof(float2);
-    const int64_t chain = z * nslab * ((cols + 255) / 256) <= (int64_t)2 << 30 ? 256 : 512;
-    p->dtg_split_a = (int)std::max<int64_t>(
-        p->dtg_split_a, std::min<int64_t>(64, (cols + chain - 1) / chain));
+  const int64_t z = p->dtg_rows * g.n1 * (int64_t)sizeof(float2);
+  for (int nslab = 1; nslab <= g.n3 && !fits[1]; ++nslab) {
+    p->dtg_s3_a = (g.n3 + nslab - 1) / nslab;
+    const int64_t cols = (int64_t)g.n2 * p->dtg_s3_a;
+    int64_t split = pow2(std::min(slots / std::max<int64_t>(1, tiles), cols / (3 * DTG_KC)), 32);
+    if (dtg_planes(p) == 3) {
+      const int64_t chain = z * nslab * ((cols + 255) / 256) <= (int64_t)2 << 30 ? 256 : 512;
+      split = std::max(split, (cols + chain - 1) / chain);
+      if (split > 64 && p->dtg_s3_a > 1) continue;
+    }
+    p->dtg_split_a = (int)std::min<int64_t>(split, 64);
+    fits[1] = dtg_workspace_bytes(p, 1) <= bound;
   }
   p->dtg_order_a = 0;
-  p->use_dtg[0] = gflop >= 0.3;
-  p->aca_dtg = gflop >= (rows_k >= 256 ? 0.4 : 1.2);
+  p->use_dtg[0] = fits[0] && gflop >= 0.3;
+  p->aca_dtg = fits[1] && gflop >= (rows_k >= 256 ? 0.4 : 1.2);
   p->use_dtg[1] = p->aca_dtg && (fused_adjoint_ws(p) > TV_STATIC_SCRATCH_BYTES ||
                                  dtg_workspace_bytes(p, 1) <= TV_STATIC_SCRATCH_BYTES);
 }
@@ -578,13 +599,22 @@ static int chain_splits(const tv_plan_s* p, int s3, int splits) {
 }
 int dtg_colgemm_splits(const tv_plan_s* p, int s3) { return chain_splits(p, s3, p->dtg_split_a); }
 
+// slabs of s3 values of i3, and how many of them have their partials of Z held
+// at once: all where those take at most 2 GiB, else as many as do
+static int64_t adjoint_slabs(const tv_plan_s* p, int s3) { return (p->grid.n3 + s3 - 1) / s3; }
+static int64_t adjoint_group(const tv_plan_s* p, int s3, int splits) {
+  const int64_t one = chain_splits(p, s3, splits) * col_zsplit(p) * (int64_t)sizeof(float2);
+  return std::min(adjoint_slabs(p, s3), std::max<int64_t>(1, ((int64_t)2 << 30) / one));
+}
+
 // adjoint workspace at slabs of s3 values of i3 and a column split count
 static size_t adjoint_ws(const tv_plan_s* p, int s3, int splits) {
   s3 = std::min(s3, p->grid.n3);
-  const int64_t nslabs = (p->grid.n3 + s3 - 1) / s3;
+  const int64_t group = adjoint_group(p, s3, splits);
   return (size_t)p->dtg_rows * dtg_ldcols(p, s3) * sizeof(float2) +
          (size_t)p->grid.q * col_ystride(p, s3) * sizeof(uint4) +
-         (size_t)nslabs * chain_splits(p, s3, splits) * col_zsplit(p) * sizeof(float2);
+         (size_t)group * chain_splits(p, s3, splits) * col_zsplit(p) * sizeof(float2) +
+         (group < adjoint_slabs(p, s3) ? p->grid.m * sizeof(double2) : 0);
 }
 
 size_t dtg_workspace_bytes(const tv_plan_s* p, int op) {
@@ -779,8 +809,22 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
     acc += p->dtg_rpad[k];
   }
   G.vec4 = (g.n1 % 2 == 0) && ((uintptr_t)z % 16 == 0);
-  int slab = 0;
-  for (int i30 = 0; i30 < g.n3; i30 += s3, ++slab) {
+  const int64_t group = adjoint_group(p, s3, splits);
+  ColReduceParams R;
+  R.meta = p->d_meta;
+  R.drow = p->d_drow;
+  R.u1t = p->d_u1t;
+  R.z = z;
+  R.x = x;
+  R.acc = group < adjoint_slabs(p, s3) ? (double2*)(z + group * S * zsplit) : nullptr;
+  for (int k = 0; k < g.q; ++k) R.brow[k] = brow[k];
+  R.zsplit = zsplit;
+  R.m = g.m;
+  R.q = g.q;
+  R.n1 = g.n1;
+  R.first = true;
+  int slab = 0;  // of the group
+  for (int i30 = 0; i30 < g.n3; i30 += s3) {
     const int s3a = std::min(s3, g.n3 - i30);
     if ((r = launch_decomp(D, dfn, dlds, g.q, i30, s3a, st)) != TV_OK) return r;
     Y.col0 = (int64_t)g.n2 * i30;
@@ -791,24 +835,18 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
                        dim3((unsigned)((yth + 255) / 256)), dim3(256), 0, st, Y);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "adjoint operand packing launch");
-    G.out = z + (int64_t)slab * S * zsplit;
+    G.out = z + (int64_t)slab++ * S * zsplit;
     if ((r = launch_split_gemm(G, gfn, threads, glds, st)) != TV_OK) return r;
+    R.last = i30 + s3 >= g.n3;
+    if (slab < group && !R.last) continue;
+    R.S = slab * S;
+    hipLaunchKernelGGL(dtg_colgemm_reduce_kernel, dim3((unsigned)g.m), dim3(RED_T), 0, st, R);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_error(e, "adjoint reduction launch");
+    R.first = false;
+    slab = 0;
   }
-  ColReduceParams R;
-  R.meta = p->d_meta;
-  R.drow = p->d_drow;
-  R.u1t = p->d_u1t;
-  R.z = z;
-  R.x = x;
-  for (int k = 0; k < g.q; ++k) R.brow[k] = brow[k];
-  R.zsplit = zsplit;
-  R.m = g.m;
-  R.q = g.q;
-  R.S = slab * S;
-  R.n1 = g.n1;
-  hipLaunchKernelGGL(dtg_colgemm_reduce_kernel, dim3((unsigned)g.m), dim3(RED_T), 0, st, R);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? TV_OK : hip_error(e, "adjoint reduction launch");
+  return TV_OK;
 }
 
 }  // namespace tv

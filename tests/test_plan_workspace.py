@@ -1,0 +1,73 @@
+"""What workspace a plan's products ask for as created, and what they do with
+other sizes."""
+import numpy as np
+import pytest
+
+from oracle import matvec as om
+from tests.plans import adj_terms, assert_close, fwd_terms, random_struct, struct_to_abi
+
+GIB = 1 << 30
+
+
+def _flat_plan(dims, q, m, r1, precision=0):
+    """A host-only plan of ranks (r1, 1, 1): its sizes are what matters."""
+    from paper_2103_06393_amd import lib
+    K = q * m
+    ones = lambda n: np.full(n, 0.5 + 0.25j)  # noqa: E731
+    return lib.tv_plan_from_factors(lib.make_grid(*dims, q, m), np.tile([r1, 1, 1], (K, 1)),
+                                    ones(K * r1), ones(K * dims[0] * r1), ones(K * dims[1]),
+                                    ones(K * dims[2]), precision)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("dims,q,m,r1", [
+    ((256, 256, 256), 3, 2048, 8),      # partials of Z as large as the slab
+    ((256, 256, 256), 12, 512, 2),
+    ((64, 512, 512), 3, 2048, 4),       # wide slabs, few rows
+    ((512, 300, 40), 3, 4000, 2),       # tall rows
+    ((256, 256, 256), 3, 1500, 1),      # one slab of 65536 columns fits
+])
+def test_new_plan_workspace_is_bounded(dims, q, m, r1, precision):
+    """At most 4 GiB each way, also for the ACA adjoint; and FP32 chains of at
+    most 512 columns in the adjoint of an FP32 plan."""
+    from paper_2103_06393_amd import lib
+    h = _flat_plan(dims, q, m, r1, precision)
+    try:
+        info = lib.tv_plan_info(h)
+        assert info.kernel[0] == 2
+        for op in (0, 1):
+            assert lib.tv_workspace_bytes(h, op, 1) <= 4 * GIB
+            assert lib.tv_aca_workspace_bytes(h, op, 1) <= 4 * GIB + 8 * m + 256
+        if info.kernel[1] == 2 and precision == 0:
+            assert dims[1] * info.tile_t2[1] <= 512 * info.splits[1]
+    finally:
+        lib.tv_plan_destroy(h)
+
+
+@pytest.mark.gpu
+def test_partials_in_groups_of_slabs(gpu_lib):
+    """64 slabs of 8 splits each, over 2 GiB of partials: held in two groups, the
+    groups' sums carried on in FP64.  Against one slab and split: FP32 sums
+    of 8 chunks at most either way, and the oracle."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    print("partials in groups: 256x8x64 x 200, 64 slabs", flush=True)
+    S = random_struct((256, 8, 64), 3, 200, 8, 21)
+    rows = S.q * S.nv
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
+    z = 8 * S.dims[0] * sum((int(P.info.sum_r1) // 3 // 16) * 16 for _ in range(3))
+    assert 64 * 8 * z > 2 * GIB                    # all partials at once pass 2 GiB
+    y = torch.randn(2, rows, dtype=torch.complex64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(4)).t()
+    lib.tv_plan_configure(P.handle, 1, path=1, slab_i3=1, splits=8, gemm_nbw=4)
+    assert lib.tv_workspace_bytes(P.handle, 1, 1) < 2 * GIB + (64 << 20)
+    a = P.rmatvec(y)
+    b = P.rmatvec(y)                               # finds the first call's workspace
+    assert torch.equal(a, b)
+    lib.tv_plan_configure(P.handle, 1, path=1, slab_i3=0, splits=1, gemm_nbw=4)
+    P._ws.clear()
+    c = P.rmatvec(y)
+    assert float((a - c).norm() / c.norm()) < 64 * 2.0 ** -24
+    Y = y.cpu().numpy()
+    assert_close(a.cpu().numpy(), om.alg2(S, Y), 1e-5, terms=adj_terms(S, Y), what="Z^* y")
