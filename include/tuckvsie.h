@@ -161,15 +161,18 @@ tv_status tv_plan_export_factors(tv_plan plan, int32_t* ranks, double* cores,
 
 /* ------------------------------------------------------------------------
  * Workspace needed by tv_matvec (op = 0) or tv_rmatvec (op = 1) for nrhs
- * right-hand sides.  May be 0; a larger workspace is always accepted.
+ * right-hand sides.  May be 0; a larger workspace is always accepted.  Until
+ * its launch configuration is set or tuned, a plan given less than this runs
+ * the fused kernels (path 0 of tv_launch_config) where theirs fits (none
+ * forward on all but small grids).
  * ---------------------------------------------------------------------- */
 tv_status tv_workspace_bytes(tv_plan plan, int32_t op, int32_t nrhs,
                              size_t* bytes);
 
 /* Y = Z X (Algorithm 1).  x: device complex64, m x nrhs, leading dim ldx
  * >= m.  y: device complex64, q*nv x nrhs, leading dim ldy >= q*nv,
- * overwritten.  ws: device workspace of at least tv_workspace_bytes(op=0)
- * bytes (may be NULL if that is 0).  x and y must not overlap.  The result
+ * overwritten.  ws: device workspace of tv_workspace_bytes(op=0)
+ * bytes (may be NULL if none is needed).  x and y must not overlap.  The result
  * is deterministic: fixed reduction order, no atomics. */
 tv_status tv_matvec(tv_plan plan, const void* x, int64_t ldx, int32_t nrhs,
                     void* y, int64_t ldy, void* ws, size_t ws_bytes,

@@ -102,9 +102,10 @@ tv_status aca_check(tv_plan p, const void* v, int64_t m, int64_t ldv, const void
   const size_t v_len = 8 * (size_t)(ldv * (rc - 1) + m);
   if (overlaps(in, in_len, out, out_len)) return set_error(TV_ERR_INVALID_ARG, "input and output overlap");
   if (overlaps(v, v_len, out, out_len)) return set_error(TV_ERR_INVALID_ARG, "V and output overlap");
+  const size_t off = align256((size_t)8 * rc * nrhs), given = ws ? ws_bytes : 0;
   size_t need = 0;
-  tv_status st = tv_aca_workspace_bytes(p, op, nrhs, &need);
-  if (st != TV_OK) return st;
+  product_dtg(p, op, true, given > off ? given - off : 0, &need);
+  need += off;
   if (!ws || ws_bytes < need) {
     char buf[128];
     snprintf(buf, sizeof buf, "workspace of %zu bytes needed, %zu given", need,
@@ -131,7 +132,7 @@ tv_status tv_aca_workspace_bytes(tv_plan p, int32_t op, int32_t nrhs, size_t* by
   size_t inner = 0;
   tv_status st = tv_workspace_bytes(p, op, nrhs, &inner);
   if (st != TV_OK) return st;
-  if (op == 1 && aca_adjoint_dtg(p)) inner = dtg_workspace_bytes(p, 1);
+  product_dtg(p, op, true, SIZE_MAX, &inner);
   *bytes = align256((size_t)8 * p->grid.m * nrhs) + inner;
   return TV_OK;
 }
@@ -167,10 +168,10 @@ tv_status tv_aca_rmatvec(tv_plan p, const void* v, int64_t m, int64_t ldv, const
   const size_t off = align256((size_t)8 * rc * nrhs);
   float2* W = (float2*)ws;
   hipStream_t s = (hipStream_t)stream;
-  st = aca_adjoint_dtg(p)
-           ? run_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off,
-                         dtg_workspace_bytes(p, 1), true, p->dtg_s3_a, p->dtg_split_a, s)
-           : tv_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off, stream);
+  size_t need = 0;
+  const bool dtg = product_dtg(p, 1, true, ws_bytes - off, &need);
+  st = run_rmatvec(p, y, ldy, nrhs, W, rc, (char*)ws + off, ws_bytes - off, need, dtg,
+                   p->dtg_s3_a, p->dtg_split_a, s);
   if (st != TV_OK) return st;
   const int64_t blocks = (m + kThreads - 1) / kThreads;
   hipLaunchKernelGGL(aca_vw_kernel, dim3((unsigned)blocks, (unsigned)nrhs), dim3(kThreads), 0, s,

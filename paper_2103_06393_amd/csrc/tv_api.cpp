@@ -92,6 +92,20 @@ size_t fused_adjoint_ws(const tv_plan_s* p) {
   return (size_t)8 * p->grid.q * p->tiling_a.tiles * p->grid.m;
 }
 
+bool product_dtg(const tv_plan_s* p, int op, bool aca, size_t avail, size_t* need) {
+  const tv_grid& g = p->grid;
+  const bool dtg = (p->use_dtg[op] || (op == 1 && aca && p->aca_dtg)) && dtg_supported(p);
+  if (dtg) {
+    *need = dtg_workspace_bytes(p, op);
+    if (avail >= *need || !p->fresh[op]) return true;
+  }
+  if (op == 1)
+    *need = fused_adjoint_ws(p);
+  else
+    *need = p->split_f > 1 ? (size_t)8 * p->split_f * g.q * g.n1 * g.n2 * g.n3 : 0;
+  return false;
+}
+
 static tv_status validate_grid(const tv_grid* g) {
   if (!g) return set_error(TV_ERR_INVALID_ARG, "grid is NULL");
   if (g->n1 < 1 || g->n2 < 1 || g->n3 < 1 || g->q < 1 || g->m < 1)
@@ -1013,14 +1027,7 @@ tv_status tv_workspace_bytes(tv_plan p, int32_t op, int32_t nrhs, size_t* bytes)
   if (op != 0 && op != 1) return set_error(TV_ERR_INVALID_ARG, "op must be 0 or 1");
   if (nrhs < 1) return set_error(TV_ERR_INVALID_ARG, "nrhs must be >= 1");
   if (!p->finalized) return set_error(TV_ERR_INVALID_ARG, "plan is not finalized");
-  const tv_grid& g = p->grid;
-  const int64_t nv = (int64_t)g.n1 * g.n2 * g.n3;
-  if (p->use_dtg[op] && dtg_supported(p))
-    *bytes = dtg_workspace_bytes(p, op);
-  else if (op == 0)
-    *bytes = p->split_f > 1 ? (size_t)8 * p->split_f * g.q * nv : 0;
-  else
-    *bytes = fused_adjoint_ws(p);
+  product_dtg(p, op, false, SIZE_MAX, bytes);
   return TV_OK;
 }
 
@@ -1061,13 +1068,14 @@ tv_status tv_matvec(tv_plan p, const void* x, int64_t ldx, int32_t nrhs, void* y
   size_t need = 0;
   tv_status st = tv_workspace_bytes(p, 0, nrhs < 1 ? 1 : nrhs, &need);
   if (st != TV_OK) return st;
+  const bool dtg = product_dtg(p, 0, false, ws ? ws_bytes : 0, &need);
   st = check_call(p, x, ldx, p->grid.m, nrhs, y, ldy, rows, ws, ws_bytes, need);
   if (st != TV_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   for (int32_t c = 0; c < nrhs; ++c) {
     const float2* xc = (const float2*)x + (int64_t)c * ldx;
     float2* yc = (float2*)y + (int64_t)c * ldy;
-    if (p->use_dtg[0] && dtg_supported(p)) {
+    if (dtg) {
       st = launch_dtg_forward(p, xc, yc, ws, s);
     } else if (p->split_f > 1) {
       st = launch_forward_f32(p, xc, (float2*)ws, p->split_f, p->d_split_f, rows, s);
@@ -1116,7 +1124,7 @@ extern "C" tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t n
   size_t need = 0;
   tv_status st = tv_workspace_bytes(p, 1, nrhs < 1 ? 1 : nrhs, &need);
   if (st != TV_OK) return st;
-  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need,
-                     p->use_dtg[1] && dtg_supported(p), p->dtg_s3_a, p->dtg_split_a,
-                     (hipStream_t)stream);
+  const bool dtg = product_dtg(p, 1, false, ws ? ws_bytes : 0, &need);
+  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need, dtg, p->dtg_s3_a,
+                     p->dtg_split_a, (hipStream_t)stream);
 }

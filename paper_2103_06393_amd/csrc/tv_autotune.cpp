@@ -167,6 +167,12 @@ static tv_status apply_config(tv_plan_s* p, int op, const tv_launch_config& c) {
   return TV_OK;
 }
 
+// The direction's configuration is no longer the new plan's own choice.
+static void config_is_set(tv_plan_s* p, int op) {
+  p->fresh[op] = false;
+  if (op == 1) p->aca_dtg = false;
+}
+
 static tv_launch_config current_config(const tv_plan_s* p, int op) {
   tv_launch_config c{};
   if (p->use_dtg[op]) {
@@ -197,8 +203,8 @@ extern "C" tv_status tv_plan_configure(tv_plan p, int32_t op, const tv_launch_co
   tv_status s = apply_config(p, op, *cfg);
   if (s != TV_OK)
     apply_config(p, op, keep);  // keeps the error message of the refusal
-  else if (op == 1)
-    p->aca_dtg = false;
+  else
+    config_is_set(p, op);
   return s;
 }
 
@@ -219,7 +225,7 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     auto it = cache.find(key);
     tv_launch_config cached{};
     if (it != cache.end() && from_vec(it->second, &cached) && apply_config(p, o, cached) == TV_OK) {
-      if (o == 1) p->aca_dtg = false;
+      config_is_set(p, o);
       continue;
     }
     std::vector<tv_launch_config> cands;
@@ -380,7 +386,7 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     }
     tv_status s = apply_config(p, o, best_c);
     if (s != TV_OK) return s;
-    if (o == 1) p->aca_dtg = false;
+    config_is_set(p, o);
     cache[key] = to_vec(best_c);
     dirty = true;
   }

@@ -549,6 +549,7 @@ void dtg_default(tv_plan_s* p) {
     fits[1] = dtg_workspace_bytes(p, 1) <= bound;
   }
   p->dtg_order_a = 0;
+  p->fresh[0] = p->fresh[1] = true;
   p->use_dtg[0] = fits[0] && gflop >= 0.3;
   p->aca_dtg = fits[1] && gflop >= (rows_k >= 256 ? 0.4 : 1.2);
   p->use_dtg[1] = p->aca_dtg && (fused_adjoint_ws(p) > TV_STATIC_SCRATCH_BYTES ||

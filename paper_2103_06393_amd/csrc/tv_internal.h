@@ -136,6 +136,7 @@ struct tv_plan_s {
   bool dtg_packed = false;          // the GEMM operands are part of the plan
   bool use_dtg[2] = {false, false};
   bool aca_dtg = false;  // tv_aca_rmatvec on the column GEMM where use_dtg[1] is not
+  bool fresh[2] = {false, false};  // the path is the new plan's own choice
   int dtg_s3 = 1 << 30;            // i3 values per slab of B (forward)
   int dtg_s3_a = 1 << 30;          // i3 values per slab of B (adjoint)
   int dtg_order_a = 0;             // adjoint GEMM workgroup order (tv_launch_config)
@@ -223,8 +224,11 @@ tv_status run_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t nrhs, void*
                       void* ws, size_t ws_bytes, size_t need, bool dtg, int s3, int splits,
                       hipStream_t s);
 size_t fused_adjoint_ws(const tv_plan_s* p);  // workspace of the fused adjoint
-// whether U^* y of tv_aca_rmatvec runs the column GEMM
-inline bool aca_adjoint_dtg(const tv_plan_s* p) { return p->use_dtg[1] || p->aca_dtg; }
+// Whether a product (op 1 with aca: U^* y of tv_aca_rmatvec) runs
+// decompress-then-GEMM in a workspace of avail bytes, and what it needs.  A
+// path that a new plan has chosen by itself gives way to the fused kernels in
+// a workspace that holds only theirs; one that was configured does not.
+bool product_dtg(const tv_plan_s* p, int op, bool aca, size_t avail, size_t* need);
 // an upper bound of the device arena of a plan of grid g whose ranks are at
 // most rmax, without the decompress-then-GEMM operands (the arena of a
 // growable plan of g.m columns)

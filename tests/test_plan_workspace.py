@@ -71,3 +71,88 @@ def test_partials_in_groups_of_slabs(gpu_lib):
     assert float((a - c).norm() / c.norm()) < 64 * 2.0 ** -24
     Y = y.cpu().numpy()
     assert_close(a.cpu().numpy(), om.alg2(S, Y), 1e-5, terms=adj_terms(S, Y), what="Z^* y")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,tol", [(0, 1e-5), (1, 1e-4)])
+@pytest.mark.parametrize("dims,m,fused", [
+    ((9, 210, 210), 24, 0),                 # enough tiles for the chip: no partials
+    ((32, 64, 24), 80, 64 * 3 * 32 * 64 * 24),      # eight partials of y
+])
+def test_new_plan_forward_in_the_fused_kernels_workspace(gpu_lib, dims, m, fused, prec, tol):
+    """A plan as created takes a call without the slab's workspace, on the
+    fused kernels; less than theirs, or a path that was set, is refused."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    print(f"fused forward's workspace, {dims}, precision {prec}", flush=True)
+    S = random_struct(dims, 3, m, 8, 17)
+    rows = S.q * S.nv
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S), precision=prec)
+    assert P.info.kernel[0] == 2 and lib.tv_workspace_bytes(P.handle, 0, 1) > fused
+    rng = np.random.default_rng(5)
+    x = (rng.standard_normal((m, 2)) + 1j * rng.standard_normal((m, 2))).astype(np.complex64)
+    xd = torch.from_numpy(np.ascontiguousarray(x.T)).cuda()
+    yd = torch.empty(2, rows, dtype=torch.complex64, device="cuda")
+    ws = torch.empty(max(fused, 16), dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+
+    def call(ptr, n):
+        lib.tv_matvec(P.handle, xd.data_ptr(), m, 2, yd.data_ptr(), rows, ptr, n, st)
+
+    call(ws.data_ptr() if fused else None, fused)
+    assert_close(yd.cpu().numpy().T, om.alg1(S, x), tol, terms=fwd_terms(S, x), what="Z x")
+    if fused:
+        with pytest.raises(lib.TuckVsieError) as e:
+            call(ws.data_ptr(), fused - 1)
+        assert e.value.status == -8
+    lib.tv_plan_configure(P.handle, 0, path=1, splits=1, gemm_nbw=4)
+    with pytest.raises(lib.TuckVsieError) as e:
+        call(ws.data_ptr(), fused)
+    assert e.value.status == -8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,tol", [(0, 1e-5), (1, 1e-4)])
+def test_new_plan_adjoint_in_the_fused_kernels_workspace(gpu_lib, prec, tol):
+    """As forward, and the ACA adjoint's second product."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    print(f"fused adjoint's workspace, precision {prec}", flush=True)
+    S = random_struct((32, 64, 24), 3, 80, 8, 17)
+    rows, mc = S.q * S.nv, S.m + 5
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S), precision=prec)
+    assert P.info.kernel[1] == 2
+    rng = np.random.default_rng(5)
+    cx = lambda *n: (rng.standard_normal(n) + 1j * rng.standard_normal(n)).astype(np.complex64)  # noqa: E731
+    y, V = cx(rows), cx(mc, S.m)
+    yd, vd = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (y, V.T))
+    xd = torch.empty(S.m, dtype=torch.complex64, device="cuda")
+    vo = torch.empty(mc, dtype=torch.complex64, device="cuda")
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    assert lib.tv_workspace_bytes(P.handle, 1, 1) > ws.numel()
+
+    def call(n):
+        lib.tv_rmatvec(P.handle, yd.data_ptr(), rows, 1, xd.data_ptr(), S.m, ws.data_ptr(), n, st)
+
+    def aca(n):
+        lib.tv_aca_rmatvec(P.handle, vd.data_ptr(), mc, mc, yd.data_ptr(), rows, 1,
+                           vo.data_ptr(), mc, ws.data_ptr(), n, st)
+
+    ref = om.alg2(S, y)[:, 0]
+    call(ws.numel())
+    assert_close(xd.cpu().numpy(), ref, tol, terms=adj_terms(S, y), what="Z^* y")
+    aca(ws.numel())
+    want = V.astype(np.complex128) @ ref
+    assert np.linalg.norm(vo.cpu().numpy() - want) < 10 * tol * np.linalg.norm(want)
+    for fn in (call, aca):
+        with pytest.raises(lib.TuckVsieError) as e:
+            fn(256)
+        assert e.value.status == -8
+    lib.tv_plan_configure(P.handle, 1, path=1, splits=1, gemm_nbw=4)
+    for fn in (call, aca):
+        with pytest.raises(lib.TuckVsieError) as e:
+            fn(ws.numel())
+        assert e.value.status == -8
