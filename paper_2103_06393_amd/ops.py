@@ -65,6 +65,32 @@ def _device_bytes(n: int) -> torch.Tensor:
     return torch.empty(max(int(n), 256), dtype=torch.uint8, device="cuda")
 
 
+class _Workspaces:
+    """The workspaces of one object's products: a buffer per operation and
+    stream, whatever the number of right-hand sides (the library takes the
+    vectors one at a time, so the sizes hardly differ).  Buffers stay until
+    clear(), also outgrown ones: captured graphs hold their addresses."""
+
+    def __init__(self):
+        self.clear()
+
+    def clear(self):
+        self._by_call = {}     # (op, nrhs, stream) -> buffer
+        self._bufs = {}        # (op, stream) -> buffers, the last one largest
+
+    def get(self, op: int, nrhs: int, stream: int, query) -> torch.Tensor:
+        """query(op, nrhs): bytes."""
+        buf = self._by_call.get((op, nrhs, stream))
+        if buf is None:
+            bufs = self._bufs.setdefault((op, stream), [])
+            if not bufs or bufs[-1].numel() < query(op, nrhs):
+                # with the coil-side vectors of up to 64 right-hand sides
+                bufs.append(torch.empty(max(query(op, -(-nrhs // 64) * 64), 16),
+                                        dtype=torch.uint8, device="cuda"))
+            buf = self._by_call[(op, nrhs, stream)] = bufs[-1]
+        return buf
+
+
 def batch_create(handles, op: int, nrhs, config=(0, 0)):
     """tv_batch_create (config = (tsplit, blocks_per_cu), zeros: automatic)
     plus its device arena: returns (batch handle, arena); the arena tensor
@@ -99,7 +125,7 @@ class TuckerPlan:
         self.m = g.m
         self.nv = g.n1 * g.n2 * g.n3
         self.rows = self.q * self.nv
-        self._ws = {}
+        self._ws = _Workspaces()
 
     @property
     def info(self) -> lib.tv_plan_info_t:
@@ -159,12 +185,8 @@ class TuckerPlan:
 
     # -- products ---------------------------------------------------------
     def workspace(self, op: int, nrhs: int) -> torch.Tensor:
-        key = (op, nrhs)
-        if key not in self._ws:
-            n = lib.tv_workspace_bytes(self.handle, op, nrhs)
-            self._ws[key] = torch.empty(max(n, 16), dtype=torch.uint8,
-                                        device="cuda")
-        return self._ws[key]
+        return self._ws.get(op, nrhs, _stream(),
+                            lambda *a: lib.tv_workspace_bytes(self.handle, *a))
 
     def matvec(self, x: torch.Tensor, out: Optional[torch.Tensor] = None):
         """Y = Z X for x of shape (m,) or (m, p), complex64 on the GPU."""
@@ -216,15 +238,11 @@ class AcaTuckerOperator:
         self.rows = plan.rows
         # column-major m x r_c: the transpose of a contiguous (r_c, m) tensor
         self.Vc = V.to(torch.complex64).t().contiguous()
-        self._ws = {}
+        self._ws = _Workspaces()
 
     def workspace(self, op: int, nrhs: int) -> torch.Tensor:
-        key = (op, nrhs)
-        if key not in self._ws:
-            n = lib.tv_aca_workspace_bytes(self.plan.handle, op, nrhs)
-            self._ws[key] = torch.empty(max(n, 16), dtype=torch.uint8,
-                                        device="cuda")
-        return self._ws[key]
+        return self._ws.get(op, nrhs, _stream(),
+                            lambda *a: lib.tv_aca_workspace_bytes(self.plan.handle, *a))
 
     def matvec(self, x: torch.Tensor) -> torch.Tensor:
         """Y = U (V^* X) for x of shape (m,) or (m, p)."""

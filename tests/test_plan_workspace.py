@@ -156,3 +156,25 @@ def test_new_plan_adjoint_in_the_fused_kernels_workspace(gpu_lib, prec, tol):
         with pytest.raises(lib.TuckVsieError) as e:
             fn(ws.numel())
         assert e.value.status == -8
+
+
+@pytest.mark.gpu
+def test_right_hand_sides_share_a_workspace(gpu_lib):
+    """One buffer per operation and stream, whatever the number of right-hand
+    sides; another stream's calls have their own."""
+    import torch
+    from paper_2103_06393_amd.ops import AcaTuckerOperator, TuckerPlan
+    S = random_struct((32, 64, 24), 3, 80, 8, 17)
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
+    V = torch.randn(S.m + 5, S.m, dtype=torch.complex64, device="cuda")
+    for obj in (P, AcaTuckerOperator(P, V)):
+        for op in (0, 1):
+            one = obj.workspace(op, 1)
+            assert all(obj.workspace(op, p) is one for p in (2, 3, 32, 1))
+        with torch.cuda.stream(torch.cuda.Stream()):
+            other = obj.workspace(1, 1)
+            assert other is obj.workspace(1, 3) and other.data_ptr() != one.data_ptr()
+    A = AcaTuckerOperator(P, V)
+    A.workspace(0, 1)
+    more = A.workspace(0, 4000)     # coil-side vectors past the first buffer
+    assert more is A.workspace(0, 1000) and A.workspace(0, 1) is not more
