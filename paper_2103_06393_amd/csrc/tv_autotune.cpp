@@ -173,21 +173,37 @@ static void config_is_set(tv_plan_s* p, int op) {
   if (op == 1) p->aca_dtg = false;
 }
 
-static tv_launch_config current_config(const tv_plan_s* p, int op) {
-  tv_launch_config c{};
-  if (p->use_dtg[op]) {
-    c.path = 1;
-    c.splits = op == 0 ? p->dtg_split : p->dtg_split_a;
-    c.slab_i3 = op == 0 ? p->dtg_s3 : p->dtg_s3_a;
-    c.gemm_nbw = op == 0 ? p->dtg_nbw : p->dtg_nbw_a;
-    c.gemm_order = op == 0 ? 0 : p->dtg_order_a;
-    c.row_cap = p->dtg_mbw[op];
-    return c;
+// One direction's whole launch configuration, of both paths: a plan on the
+// fused kernels also holds the slab and splits that tv_aca_rmatvec may run.
+struct SavedConfig {
+  Tiling tiling;
+  int cap, split, s3, nbw, dtg_split, order, mbw;
+  bool dtg;
+};
+static SavedConfig save_config(const tv_plan_s* p, int op) {
+  return op == 0 ? SavedConfig{p->tiling, 0, p->split_f, p->dtg_s3, p->dtg_nbw, p->dtg_split, 0,
+                               p->dtg_mbw[0], p->use_dtg[0]}
+                 : SavedConfig{p->tiling_a, p->nbcap_a, p->split_a, p->dtg_s3_a, p->dtg_nbw_a,
+                               p->dtg_split_a, p->dtg_order_a, p->dtg_mbw[1], p->use_dtg[1]};
+}
+static void restore_config(tv_plan_s* p, int op, const SavedConfig& c) {
+  if (op == 0) {
+    p->tiling = c.tiling;
+    p->dtg_s3 = c.s3;
+    p->dtg_nbw = c.nbw;
+    p->dtg_split = c.dtg_split;
+  } else {
+    p->tiling_a = c.tiling;
+    p->nbcap_a = c.cap;
+    p->dtg_s3_a = c.s3;
+    p->dtg_nbw_a = c.nbw;
+    p->dtg_split_a = c.dtg_split;
+    p->dtg_order_a = c.order;
   }
-  c.tile_t2 = op == 0 ? p->tiling.t2 : p->tiling_a.t2;
-  c.splits = op == 0 ? p->split_f : p->split_a;
-  c.row_cap = nb_cap(p, op);
-  return c;
+  p->dtg_mbw[op] = c.mbw;
+  p->use_dtg[op] = c.dtg;
+  // the table only where a candidate replaced it
+  if ((op == 0 ? p->split_f : p->split_a) != c.split) set_split(p, op, c.split);
 }
 
 }  // namespace tv
@@ -199,10 +215,10 @@ extern "C" tv_status tv_plan_configure(tv_plan p, int32_t op, const tv_launch_co
   if (!p || !cfg) return set_error(TV_ERR_INVALID_ARG, "plan and cfg must be non-NULL");
   if (!p->finalized) return set_error(TV_ERR_INVALID_ARG, "plan is not finalized");
   if (op != 0 && op != 1) return set_error(TV_ERR_INVALID_ARG, "op must be 0 or 1");
-  const tv_launch_config keep = current_config(p, op);
+  const SavedConfig keep = save_config(p, op);
   tv_status s = apply_config(p, op, *cfg);
   if (s != TV_OK)
-    apply_config(p, op, keep);  // keeps the error message of the refusal
+    restore_config(p, op, keep);
   else
     config_is_set(p, op);
   return s;
@@ -264,10 +280,10 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
           c.slab_i3 = slab;
           c.gemm_nbw = nbw;
           c.splits = 1;
-          const tv_launch_config keep = current_config(p, o);
+          const SavedConfig keep = save_config(p, o);
           if (apply_config(p, o, c) != TV_OK) continue;
           const size_t need = dtg_workspace_bytes(p, o);
-          apply_config(p, o, keep);
+          restore_config(p, o, keep);
           if (need > ((size_t)16 << 30)) continue;
           if (o == 1) {
             // the column GEMM: both tiles and workgroup orders, every
@@ -329,15 +345,13 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     }
     // buffers sized for the largest candidate
     size_t wsb = 16;
-    {
-      const tv_launch_config keep = current_config(p, o);
-      for (const auto& c : cands) {
-        if (apply_config(p, o, c) != TV_OK) continue;
-        size_t b = 0;
-        if (tv_workspace_bytes(p, o, 1, &b) == TV_OK) wsb = std::max(wsb, b);
-      }
-      apply_config(p, o, keep);
+    const SavedConfig keep = save_config(p, o);
+    for (const auto& c : cands) {
+      if (apply_config(p, o, c) != TV_OK) continue;
+      size_t b = 0;
+      if (tv_workspace_bytes(p, o, 1, &b) == TV_OK) wsb = std::max(wsb, b);
     }
+    restore_config(p, o, keep);
     void *x = nullptr, *y = nullptr, *ws = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipMalloc(&x, (size_t)8 * g.m);
@@ -347,9 +361,8 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     if (e == hipSuccess) e = hipMemsetAsync(y, 0, (size_t)8 * rows, st);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    const tv_launch_config keep = current_config(p, o);
     float best = -1.f;
-    tv_launch_config best_c = keep;
+    tv_launch_config best_c{};
     for (size_t a = 0; e == hipSuccess && a < cands.size(); ++a) {
       if (apply_config(p, o, cands[a]) != TV_OK) continue;
       auto run = [&]() {
@@ -380,8 +393,11 @@ extern "C" tv_status tv_autotune(tv_plan p, int32_t op, const char* cache_path, 
     hipFree(x);
     hipFree(y);
     hipFree(ws);
-    if (e != hipSuccess) {
-      apply_config(p, o, keep);
+    if (e != hipSuccess || best < 0.f) {
+      // the plan as it was; the next launch's check must not find this error
+      restore_config(p, o, keep);
+      (void)hipGetLastError();
+      if (e == hipSuccess) continue;
       return hip_error(e, "tv_autotune");
     }
     tv_status s = apply_config(p, o, best_c);

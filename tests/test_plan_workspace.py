@@ -178,3 +178,31 @@ def test_right_hand_sides_share_a_workspace(gpu_lib):
     A.workspace(0, 1)
     more = A.workspace(0, 4000)     # coil-side vectors past the first buffer
     assert more is A.workspace(0, 1000) and A.workspace(0, 1) is not more
+
+
+@pytest.mark.gpu
+def test_failed_autotune_leaves_the_plan(gpu_lib):
+    """The tuner's vectors do not fit the card: it reports that, the plan keeps
+    its configuration (also the one that only the ACA adjoint runs), and the
+    next product is not blamed for it."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    dims, q, n = (512, 2700, 2700), 12, 12
+    assert 8 * q * np.prod(dims, dtype=np.int64) > torch.cuda.mem_get_info()[1]
+    rng = np.random.default_rng(2)
+    f = lambda k: rng.standard_normal(n * k) + 0j  # noqa: E731
+    P = TuckerPlan.from_factors(dims, q, 1, np.ones((n, 3), np.int32), f(1),
+                                *(f(d) for d in dims))
+    before = bytes(P.info), [lib.tv_aca_workspace_bytes(P.handle, op, 1) for op in (0, 1)]
+    assert P.info.kernel[1] != 2 and before[1][1] > lib.tv_workspace_bytes(P.handle, 1, 1) + 512
+    for op in (1, 0, 2):
+        with pytest.raises(lib.TuckVsieError) as e:
+            P.autotune(op)
+        assert e.value.status in (-4, -5)
+        assert (bytes(P.info), [lib.tv_aca_workspace_bytes(P.handle, o, 1)
+                                for o in (0, 1)]) == before
+    S = random_struct((20, 13, 7), 2, 5, 5, 72)
+    Q = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
+    x = torch.ones(S.m, dtype=torch.complex64, device="cuda")
+    assert torch.isfinite(torch.view_as_real(Q.matvec(x))).all()
