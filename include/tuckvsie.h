@@ -230,9 +230,9 @@ tv_status tv_plan_configure(tv_plan plan, int32_t op, const tv_launch_config* cf
  * adjoint's scratch is a static device array of TV_STATIC_SCRATCH_BYTES per
  * GPU, held until the process ends; a plan configuration needing more
  * (tv_workspace_bytes(plan, 1, nrhs)) returns TV_ERR_WORKSPACE before any
- * device work, except that path 1 takes lower slabs where only its packed y
- * does not fit (its result then differs from tv_rmatvec's in rounding).  All calls on one GPU share the array: calls that overlap in
- * time on one GPU (different streams or threads) race and must be
+ * device work, except that both calls take lower slabs on path 1 where only
+ * its packed y does not fit.  All calls on one GPU share the array: calls that
+ * overlap in time on one GPU (different streams or threads) race and must be
  * serialised by the caller.  Every scratch entry a call reads is written
  * earlier in the same call, so nothing carries over between calls. */
 #define TV_STATIC_SCRATCH_BYTES (32u << 20)

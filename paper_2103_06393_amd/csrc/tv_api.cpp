@@ -1125,6 +1125,12 @@ extern "C" tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t n
   tv_status st = tv_workspace_bytes(p, 1, nrhs < 1 ? 1 : nrhs, &need);
   if (st != TV_OK) return st;
   const bool dtg = product_dtg(p, 1, false, ws ? ws_bytes : 0, &need);
-  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need, dtg, p->dtg_s3_a,
-                     p->dtg_split_a, (hipStream_t)stream);
+  // the slabs that tv_rmatvec_noalloc runs, where it can: its bits are these
+  int s3 = p->dtg_s3_a, splits = p->dtg_split_a;
+  if (dtg && !dtg_adjoint_within(p, TV_STATIC_SCRATCH_BYTES, &s3, &splits)) {
+    s3 = p->dtg_s3_a;
+    splits = p->dtg_split_a;
+  }
+  return run_rmatvec(p, y, ldy, nrhs, x, ldx, ws, ws_bytes, need, dtg, s3, splits,
+                     (hipStream_t)stream);
 }

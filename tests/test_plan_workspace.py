@@ -206,3 +206,26 @@ def test_failed_autotune_leaves_the_plan(gpu_lib):
     Q = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
     x = torch.ones(S.m, dtype=torch.complex64, device="cuda")
     assert torch.isfinite(torch.view_as_real(Q.matvec(x))).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,m,rmax,splits", [((64, 64, 40), 104, 6, 1), ((64, 64, 40), 104, 6, 4),
+                                                ((48, 64, 45), 85, 7, 3)])
+def test_noalloc_has_rmatvecs_bits_in_lower_slabs(gpu_lib, dims, m, rmax, splits):
+    """Where the static scratch takes the adjoint in lower slabs only, both
+    calls run those."""
+    import torch
+    from paper_2103_06393_amd import lib
+    from paper_2103_06393_amd.ops import TuckerPlan
+    print(f"noalloc bits {dims} x {m}, {splits} splits", flush=True)
+    S = random_struct(dims, 3, m, rmax, 9)
+    P = TuckerPlan.from_factors(S.dims, S.q, S.m, *struct_to_abi(S))
+    lib.tv_plan_configure(P.handle, 1, path=1, splits=splits, gemm_nbw=4)
+    assert lib.tv_workspace_bytes(P.handle, 1, 1) > lib.TV_STATIC_SCRATCH_BYTES
+    rows = S.q * S.nv
+    y = torch.randn(rows, dtype=torch.complex64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(4))
+    x = torch.empty(S.m, dtype=torch.complex64, device="cuda")
+    lib.tv_rmatvec_noalloc(P.handle, y.data_ptr(), rows, 1, x.data_ptr(), S.m,
+                           torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(x, P.rmatvec(y))
