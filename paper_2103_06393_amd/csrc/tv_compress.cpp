@@ -272,8 +272,9 @@ tv_status compress_append_staged(tv_plan p, const void* cols, int64_t ncols, voi
   double2* dS;
   double2* dP;  // partial Gram tiles of calls with few tensors, as far as there is room
   size_t npart = gram_partial_count(T, nmax, false);
-  const size_t rest = scratch_bytes(p, T, 0);
-  npart = std::min(npart, ws_bytes > rest ? (ws_bytes - rest) / sizeof(double2) : 0);
+  // (scratch without them still holds a 256-byte piece for them)
+  const size_t room = (ws_bytes - scratch_bytes(p, T, 0) + 256) / 256 * 256;
+  npart = std::min(npart, room / sizeof(double2));
   if ((s = ds.alloc(&dS, (size_t)3 * T * mat)) != TV_OK) return s;
   if ((s = ds.alloc(&dP, npart)) != TV_OK) return s;
   if ((s = launch_gram(A, T, g.n1, g.n2, g.n3, nmax, dS, dP, npart, st)) != TV_OK) return s;

@@ -54,3 +54,30 @@ def test_shorter_last_chunk_compresses_as_one(gpu_lib):
                     generator=torch.Generator(device="cuda").manual_seed(1))
     ya, yb = (P.matvec(x) for P in plans)
     assert float((ya - yb).norm() / yb.norm()) < 1e-5
+
+
+@pytest.mark.gpu
+def test_asked_workspace_holds_all_partial_tiles(gpu_lib):
+    """The workspace that is asked for runs the column ranges that a larger one
+    runs, so the factors have the same bits."""
+    import torch
+    import workloads
+    from paper_2103_06393_amd import lib
+    print("compress 32^3, a column, two workspaces", flush=True)
+    wl = workloads.make("c1")
+    n, dims = 1, wl.grid.dims       # one column: 64 ranges, no smaller call asks for more
+    st = torch.cuda.current_stream().cuda_stream
+    cols = torch.empty(n * 3 * 32 ** 3 * 2, dtype=torch.float64, device="cuda")
+    lib.tv_dipole_columns(*dims, wl.grid.h, wl.k0, 0, wl.pos[:n], wl.ori[:n], cols.data_ptr(), st)
+    out = []
+    for more in (0, 1 << 24):
+        h = lib.tv_compress_begin(lib.make_grid(*dims, 3, n), 1e-4, 1, 12)
+        try:
+            nb = lib.tv_compress_workspace_bytes(h, n) + more
+            ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+            lib.tv_compress_append(h, cols.data_ptr(), n, ws.data_ptr(), nb, st)
+            out.append(lib.tv_plan_export_factors(h))
+        finally:
+            lib.tv_plan_destroy(h)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
