@@ -141,6 +141,7 @@ static size_t arena_layout(tv_plan_s* p, char* base) {
   carve(&p->d_split_a, splits);
   carve(&p->d_abf, (p->dtg_abfoff.empty() ? 0 : p->dtg_abfoff.back()) * sizeof(uint4));
   carve(&p->d_drow, h.drow.size() * sizeof(int32_t));
+  carve(&p->d_scale, h.drow.size() * sizeof(float2));
   return (off + 255) & ~(size_t)255;
 }
 
@@ -153,6 +154,7 @@ static void clear_device_pointers(tv_plan_s* p) {
   p->d_split_f = p->d_split_a = nullptr;
   p->d_abf = nullptr;
   p->d_drow = nullptr;
+  p->d_scale = nullptr;
   p->bound = false;
 }
 
@@ -446,7 +448,8 @@ static tv_status bind_arena(tv_plan_s* p, void* arena, size_t bytes, hipStream_t
   put(p->d_apack_koff, p->apack_koff.data(), p->apack_koff.size() * sizeof(int64_t));
   put(p->d_drow, h.drow.data(), h.drow.size() * sizeof(int32_t));
   if (e == hipSuccess && p->d_abf) {
-    const tv_status s = launch_dtg_pack(p, st);
+    tv_status s = launch_dtg_scale(p, 0, st);
+    if (s == TV_OK) s = launch_dtg_pack(p, st);
     if (s != TV_OK) {
       (void)hipStreamSynchronize(st);
       clear_device_pointers(p);
@@ -595,6 +598,7 @@ static size_t capacity_layout(const tv_grid& g, const int rmax[3], int nbt,
   carve(&d->d_split_f, (size_t)g.q * (TV_SPLIT_MAX + 1) * sizeof(int32_t));
   carve(&d->d_split_a, (size_t)g.q * (TV_SPLIT_MAX + 1) * sizeof(int32_t));
   carve(&d->d_drow, K * sizeof(int32_t));
+  carve(&d->d_scale, K * sizeof(float2));
   const size_t stage = stage_size(g, rmax, nbt, precision);
   carve(&d->d_stage, stage);
   if (p && base) p->stage_bytes = stage;
@@ -926,7 +930,8 @@ tv_status grow_plan_append(tv_plan p, const int32_t* ranks, const double* cores,
   tv_status cs = launch_segment_copy(segs, nseg, p->d_stage, st);
   if (cs != TV_OK) return cs;
   e = hipStreamSynchronize(st);
-  return e == hipSuccess ? TV_OK : hip_error(e, "growable plan upload");
+  if (e != hipSuccess) return hip_error(e, "growable plan upload");
+  return p->dtg_packed ? launch_dtg_scale(p, j, st) : TV_OK;
 }
 
 }  // namespace tv
@@ -1125,9 +1130,10 @@ extern "C" tv_status tv_rmatvec(tv_plan p, const void* y, int64_t ldy, int32_t n
   tv_status st = tv_workspace_bytes(p, 1, nrhs < 1 ? 1 : nrhs, &need);
   if (st != TV_OK) return st;
   const bool dtg = product_dtg(p, 1, false, ws ? ws_bytes : 0, &need);
-  // the slabs that tv_rmatvec_noalloc runs, where it can: its bits are these
+  // the slabs that tv_rmatvec_noalloc runs, where it can (not on an assembly's
+  // own plan): its bits are these
   int s3 = p->dtg_s3_a, splits = p->dtg_split_a;
-  if (dtg && !dtg_adjoint_within(p, TV_STATIC_SCRATCH_BYTES, &s3, &splits)) {
+  if (p->grow_mcap || (dtg && !dtg_adjoint_within(p, TV_STATIC_SCRATCH_BYTES, &s3, &splits))) {
     s3 = p->dtg_s3_a;
     splits = p->dtg_split_a;
   }

@@ -26,19 +26,60 @@ struct DecompParams {
   const float2* u2t;
   const float2* u3t;
   const float2* x;   // x_j scaling (forward) or null
+  const float2* scale;  // see dtg_scale_kernel
   const int32_t* drow;  // first stacked row of each tensor [k * m + j]
   float2* B;         // layout as SplitGemmParams::b
   int64_t boff[DTG_MAXQ];
-  int32_t rpad[DTG_MAXQ];
+  int32_t rk[DTG_MAXQ], rpad[DTG_MAXQ];
   int lw;
   int64_t m;
-  int n2, n3, i30, s3, nsub;
+  int q, n2, n3, i30, s3, nsub;
   int t3w;           // i3 values per decompression workgroup
   int64_t nitems;
 };
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+// 1 / v of a power of two between 2^-126 and 2^126
+__device__ __forceinline__ float pow2_inv(float v) {
+  return __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, v));
+}
+
+// The powers of two that bring a tensor's operands of the GEMMs near 1, from
+// the largest real or imaginary parts of its factors, at plan set-up, a wave a
+// factor: scale[k + q j] = (of modes 2 and 3, 1 / of U1).  The adjoint's B is
+// decompressed with the first and the final sum takes it back; U1 is packed
+// divided by the second, and the forward's B decompressed with it (1 unless U1
+// is below 2^-10, which orthonormal columns are not).
+__global__ __launch_bounds__(256) void dtg_scale_kernel(const TensorMeta* meta, const float2* cores,
+                                                        const float2* u1t, const float2* u2t,
+                                                        const float2* u3t, float2* scale, int q,
+                                                        int64_t m, int64_t j0, int n1, int n2,
+                                                        int n3) {
+  __shared__ int ex[4];
+  const int64_t j = j0 + blockIdx.x;
+  const int k = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const TensorMeta t = meta[(int64_t)k * m + j];
+  const float2* v = wave == 0 ? cores + t.g_off
+                    : wave == 1 ? u1t + t.u1_off : wave == 2 ? u2t + t.u2_off : u3t + t.u3_off;
+  const int n = wave == 0 ? t.r1 * t.r2 * t.r3
+                : wave == 1 ? n1 * t.r1 : wave == 2 ? n2 * t.r2 : n3 * t.r3;
+  int top = 0;
+  for (int i = lane; i < n; i += 64) {
+    const float2 u = v[i];
+    top = max(top, max(__builtin_bit_cast(int, u.x) & 0x7FFFFFFF,
+                       __builtin_bit_cast(int, u.y) & 0x7FFFFFFF));
+  }
+  for (int off = 32; off > 0; off >>= 1) top = max(top, __shfl_xor(top, off));
+  if (lane == 0) ex[wave] = top ? (top >> 23) - 127 : 0;
+  __syncthreads();
+  if (threadIdx.x) return;
+  const auto pow2 = [](int e) {
+    return __builtin_bit_cast(float, (127 + min(max(e, -100), 100)) << 23);
+  };
+  scale[k + q * j] = make_float2(pow2(-ex[0] - ex[2] - ex[3]), pow2(ex[1] < -10 ? ex[1] : 0));
 }
 
 // B rows of one tensor for cnt <= t3w values of i3, two small products:
@@ -85,7 +126,10 @@ __global__ __launch_bounds__(DEC_T) void dtg_decomp_kernel(DecompParams P) {
   const int np = r1 * cnt, nrow = dec_rows(r1, cnt), rb = dec_rb(r2);
   float* Hs = reinterpret_cast<float*>(dsm);          // [part][p][b]
   int2* tab = reinterpret_cast<int2*>(Hs + (size_t)2 * nrow * rb);
-  const float2 xj = P.x ? P.x[j] : make_float2(1.f, 0.f);
+  const int row0 = P.drow[kt];
+  const float2 sc = P.scale[k + P.q * j];
+  const float2 xj = P.x ? P.x[j] : make_float2(sc.x, 0.f);
+  const float su = P.x ? sc.y : 1.f;
   const float2* G = P.cores + t.g_off;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -134,7 +178,8 @@ __global__ __launch_bounds__(DEC_T) void dtg_decomp_kernel(DecompParams P) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (i0 + i >= cnt) break;
-      const float2 v = cmul(xj, s[i]);
+      float2 v = cmul(xj, s[i]);
+      if (su != 1.f) v = make_float2(v.x * su, v.y * su);
       float* d = Hs + ((i0 + i) * r1 + a) * rb + b;
       d[0] = v.x;
       d[(size_t)nrow * rb] = v.y;
@@ -147,13 +192,31 @@ __global__ __launch_bounds__(DEC_T) void dtg_decomp_kernel(DecompParams P) {
     Hs[p * rb + b] = 0.f;
     Hs[(size_t)(nrow + p) * rb + b] = 0.f;
   }
+  // zeros where the GEMM's K is padded: forward the rows past the last tensor's
+  // (the workgroup's columns of every m-th one), adjoint this tensor's columns
+  // past the slab's last
+  if (P.x) {
+    for (int64_t row = P.rk[k] + j; row < P.rpad[k]; row += P.m)
+      for (int e = tid; e < cnt * P.n2; e += DEC_T) {
+        const int n = (i3a - P.i30) * P.n2 + e;
+        P.B[P.boff[k] + (((int64_t)(n >> P.lw) * P.rpad[k] + row) << P.lw) +
+            (n & ((1 << P.lw) - 1))] = make_float2(0.f, 0.f);
+      }
+  } else if (sub == P.nsub - 1) {
+    const int64_t n0 = (int64_t)P.s3 * P.n2, pad = (n0 + DTG_KC - 1) / DTG_KC * DTG_KC - n0;
+    for (int e = tid; e < pad * r1; e += DEC_T) {
+      const int64_t n = n0 + e / r1;
+      P.B[P.boff[k] + (((n >> P.lw) * P.rpad[k] + row0 + e % r1) << P.lw) +
+          (n & ((1 << P.lw) - 1))] = make_float2(0.f, 0.f);
+    }
+  }
   for (int p = tid; p < np; p += DEC_T) {
     const int i3l = p / r1;
     tab[p] = make_int2((i3a - P.i30 + i3l) * P.n2, (p - i3l * r1) << P.lw);
   }
   __syncthreads();
 
-  float2* Bk = P.B + P.boff[k] + ((int64_t)P.drow[kt] << P.lw);
+  float2* Bk = P.B + P.boff[k] + ((int64_t)row0 << P.lw);
   const uint64_t bblk = (uint64_t)P.rpad[k] << P.lw;  // one block of columns
   const int nmask = (1 << P.lw) - 1;
   for (int task = task0; task < task1; ++task) {
@@ -202,6 +265,7 @@ __global__ __launch_bounds__(DEC_T) void dtg_decomp_kernel(DecompParams P) {
 // 8 c + 4 h + e, part t); rows past n1 and past the stacked rows are zeros.
 struct APackParams {
   const TensorMeta* meta;
+  const float2* scale;
   const int32_t* drow;
   const float2* u1t;
   uint4* a;
@@ -215,6 +279,7 @@ template <int NS>
 __global__ __launch_bounds__(256) void dtg_apack_kernel(APackParams P) {
   __shared__ const float2* src[8];  // U1 column of each stacked row of the chunk
   __shared__ int ld[8];
+  __shared__ float up[8];
   int k = 0;
   while ((int)blockIdx.x >= P.cpre[k + 1]) ++k;
   const int c = (int)blockIdx.x - P.cpre[k];
@@ -222,6 +287,7 @@ __global__ __launch_bounds__(256) void dtg_apack_kernel(APackParams P) {
     const int row = 8 * c + threadIdx.x;
     src[threadIdx.x] = nullptr;
     ld[threadIdx.x] = 0;
+    up[threadIdx.x] = 0.f;
     if (row < P.rk[k]) {
       // the last tensor whose first stacked row is at or before this one
       const int32_t* d = P.drow + (int64_t)k * P.m;
@@ -234,6 +300,7 @@ __global__ __launch_bounds__(256) void dtg_apack_kernel(APackParams P) {
       const TensorMeta t = P.meta[(int64_t)k * P.m + lo];
       src[threadIdx.x] = P.u1t + t.u1_off + (row - d[lo]);
       ld[threadIdx.x] = t.r1;
+      up[threadIdx.x] = pow2_inv(P.scale[k + P.q * lo].y);
     }
   }
   __syncthreads();
@@ -246,6 +313,7 @@ __global__ __launch_bounds__(256) void dtg_apack_kernel(APackParams P) {
       const float2* col = src[4 * h + e];
       float2 v = make_float2(0.f, 0.f);
       if (col && i1 < P.n1) v = col[(int64_t)i1 * ld[4 * h + e]];
+      v = make_float2(v.x * up[4 * h + e], v.y * up[4 * h + e]);
       bf_split<NS>(s ? v.y : v.x, s ? v.x : -v.y, w[e]);
     }
     uint4* dst = P.a + P.aoff[k] + ((int64_t)c * P.nbtp + blk) * NS * 64 + lane;
@@ -299,6 +367,10 @@ __global__ void dtg_ypack_kernel(YPackParams P) {
       v0 = sr == 0 ? y.x : y.y;
       v1 = sr == 0 ? y.y : -y.x;
     }
+    if (NS == 3) {
+      v0 *= SPLIT_UP;
+      v1 *= SPLIT_UP;
+    }
     bf_split<NS>(v0, v1, w[j]);
   }
   uint4* dst = P.yp + (int64_t)k * P.ystride + (c * P.nbtp + blk) * NS * 64 + lane;
@@ -317,6 +389,7 @@ __global__ void dtg_ypack_kernel(YPackParams P) {
 // one thread per i1 over all rows; 64^3 x 256 39 -> 7 us.
 struct ColReduceParams {
   const TensorMeta* meta;
+  const float2* scale;
   const int32_t* drow;
   const float2* u1t;
   const float2* z;
@@ -337,6 +410,7 @@ __global__ __launch_bounds__(RED_T) void dtg_colgemm_reduce_kernel(ColReducePara
   for (int k = 0; k < P.q; ++k) {
     const TensorMeta t = P.meta[(int64_t)k * P.m + j];
     const float2* zk = P.z + (P.brow[k] + P.drow[(int64_t)k * P.m + j]) * P.n1;
+    const double up = pow2_inv(P.scale[k + P.q * j].x);  // Z is of the scaled tensor
     for (int a = (wave - turn) & (RED_T / 64 - 1); a < t.r1; a += RED_T / 64) {
       for (int i1 = lane; i1 < P.n1; i1 += 64) {
         const float2 u = P.u1t[t.u1_off + (int64_t)i1 * t.r1 + a];
@@ -358,7 +432,7 @@ __global__ __launch_bounds__(RED_T) void dtg_colgemm_reduce_kernel(ColReducePara
           zr += v.x;
           zi += v.y;
         }
-        const double ur = u.x, ui = u.y;
+        const double ur = u.x * up, ui = u.y * up;
         sr += ur * zr + ui * zi;
         si += ur * zi - ui * zr;
       }
@@ -465,10 +539,20 @@ tv_status dtg_layout(tv_plan_s* p, const std::vector<TensorMeta>& meta) {
   return TV_OK;
 }
 
+tv_status launch_dtg_scale(const tv_plan_s* p, int64_t j0, hipStream_t st) {
+  const tv_grid& g = p->grid;
+  hipLaunchKernelGGL(dtg_scale_kernel, dim3((unsigned)(g.m - j0), g.q), dim3(256), 0, st,
+                     p->d_meta, p->d_cores, p->d_u1t, p->d_u2t, p->d_u3t, p->d_scale, g.q, g.m, j0,
+                     g.n1, g.n2, g.n3);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? TV_OK : hip_error(e, "operand scale launch");
+}
+
 tv_status launch_dtg_pack(const tv_plan_s* p, hipStream_t st) {
   const tv_grid& g = p->grid;
   APackParams P;
   P.meta = p->d_meta;
+  P.scale = p->d_scale;
   P.drow = p->d_drow;
   P.u1t = p->d_u1t;
   P.a = p->d_abf;
@@ -656,6 +740,7 @@ static tv_status decomp_setup(const tv_plan_s* p, const float2* x, float2* B, in
   D->u2t = p->d_u2t;
   D->u3t = p->d_u3t;
   D->x = x;
+  D->scale = p->d_scale;
   D->drow = p->d_drow;
   D->B = B;
   D->lw = lw;
@@ -663,9 +748,11 @@ static tv_status decomp_setup(const tv_plan_s* p, const float2* x, float2* B, in
   int64_t acc = 0;
   for (int k = 0; k < g.q; ++k) {
     D->boff[k] = acc;
+    D->rk[k] = (int32_t)p->sum_r1_k[k];
     D->rpad[k] = (int32_t)p->dtg_rpad[k];
     acc += p->dtg_rpad[k] * ldcols;
   }
+  D->q = g.q;
   D->m = g.m;
   D->n2 = g.n2;
   D->n3 = g.n3;
@@ -705,6 +792,8 @@ static tv_status gemm_setup(const tv_plan_s* p, const DecompParams& D, bool adj,
     G->rk[k] = (int32_t)p->sum_r1_k[k];
     G->rpad[k] = (int32_t)p->dtg_rpad[k];
   }
+  G->y = nullptr;
+  G->nv = (int64_t)g.n1 * g.n2 * g.n3;
   G->q = g.q;
   G->nbtp = p->dtg_nbtp;
   G->mtiles = p->dtg_nbtp / mt;
@@ -813,6 +902,7 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
   const int64_t group = adjoint_group(p, s3, splits);
   ColReduceParams R;
   R.meta = p->d_meta;
+  R.scale = p->d_scale;
   R.drow = p->d_drow;
   R.u1t = p->d_u1t;
   R.z = z;
@@ -830,6 +920,7 @@ tv_status launch_dtg_adjoint(const tv_plan_s* p, const float2* y, float2* x, voi
     if ((r = launch_decomp(D, dfn, dlds, g.q, i30, s3a, st)) != TV_OK) return r;
     Y.col0 = (int64_t)g.n2 * i30;
     Y.ncols = G.ncols = (int64_t)g.n2 * s3a;
+    G.y = y + Y.col0 * g.n1;
     Y.nchk = (Y.ncols + DTG_KC - 1) / DTG_KC * 2;
     const int64_t yth = (int64_t)g.q * Y.nchk * Y.nbtp * 64;
     hipLaunchKernelGGL(bf16 ? dtg_ypack_kernel<2> : dtg_ypack_kernel<3>,

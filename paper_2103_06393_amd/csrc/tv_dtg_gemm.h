@@ -8,9 +8,8 @@
 //
 // Operands are split into NS bf16 planes, x = h + m + l with h = rn(x),
 // m = rn(x - h), l = rn(x - h - m):
-//   NS = 3 (FP32 plans): the 24 bits of an FP32 value exactly (|x| >= 2^-110;
-//     below that the low plane runs out of exponent), and of the nine partial
-//     products the six of weight 2^-16 and above: hh, hm, mh, hl, mm, lh.
+//   NS = 3 (FP32 plans): the 24 bits of an FP32 value exactly, and of the nine
+//     partial products the six of weight 2^-16 and above: hh, hm, mh, hl, mm, lh.
 //     The dropped ml + lm + ll is below 2^-23 |ab|, 2^-25 rms: under the
 //     rounding of one FP32 product and sum.  v_mfma_f32_32x32x16_bf16 rounds
 //     to FP32 after every 8 products (measured: K = 16 has the error of two
@@ -21,6 +20,14 @@
 //     where the terms' signs are random and U1 is smooth; odd chunks form the
 //     negated products and are subtracted, which cancels it (adjoint of 512
 //     dipole columns on 128^3, random y: error 3.2e-6 without, 4.9e-7 with).
+//     The low plane runs out of exponent below 2^-110: the plan's operand (U1;
+//     the adjoint's B) is brought near 1, each tensor by itself, and what a
+//     call brings (y; B with x in it) is split as 2^17 times itself, which the
+//     running sum takes back as it adds a chunk.  A wave whose sums are not
+//     finite (an infinity or NaN among its operands, or products from about
+//     2^110 on) forms them again on v_mfma_f32_32x32x2f32 from the FP32
+//     operands (128^3 x 256 adjoint: 1.1 ms, 3.9 with one infinity in y, 8.3
+//     where every wave does).
 //   NS = 2 (BF16X3 plans): hh, hl, lh.
 //
 // One LDS stage is a chunk of 16 real k-steps (8 stacked rows, or 8 columns,
@@ -30,7 +37,7 @@
 // memory to LDS, and lands in operand order ([plane][h][column], 16 bytes:
 // every LDS access of the loop is a conflict-free 16-byte one).  Chunk c + 2
 // is loaded into registers while chunk c is multiplied and chunk c + 1 goes
-// from registers to the other LDS buffer half way through c's products; one
+// from registers to the other LDS buffer about half way through c's products; one
 // barrier per chunk.
 //
 // Tile: MT = WM MBW blocks of 32 rows (all of 2 n1 rows in ceil(n1/128)
@@ -65,7 +72,8 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // B: the slab of component k, complex64 in blocks of 2^lw columns: entry
-// (row, n) at boff[k] + ((n >> lw) rpad[k] + row) 2^lw + n % 2^lw.  lw = 8
+// (row, n) at boff[k] + ((n >> lw) rpad[k] + row) 2^lw + n % 2^lw, with zeros
+// where K is padded (forward rows up to rpad, adjoint columns up to 16).  lw = 8
 // forward (a workgroup streams whole rows of its columns), lw = 5 adjoint (a
 // chunk reads 64 bytes of every row; at 256^3 x 512 the decompression writes
 // blocks of 8 columns, 64 bytes, in 2.2 ms, of 16 or 32 in 1.3 ms, and the
@@ -85,6 +93,8 @@ struct SplitGemmParams {
   int q, nbtp, mtiles, S;
   int order;                // 0: row tiles fastest, 1: N tiles fastest
   int n1;
+  const float2* y;          // adjoint: y of the slab's first column, and per component
+  int64_t nv;
   int64_t ncols;            // columns of the slab
   int vec4;
   int64_t nitems;
@@ -99,21 +109,24 @@ inline size_t split_gemm_lds(int ns, int mt, int ncol) {
   return 2 * sizeof(uint4) * (size_t)(mt * ns * 64 + ns * 2 * (ncol + 8));
 }
 
+// scale of a call's operand as it is split into three planes
+constexpr float SPLIT_UP = 131072.f;
+
 __device__ __forceinline__ v8bf as_v8bf(v4u v) { return __builtin_bit_cast(v8bf, v); }
 __device__ __forceinline__ uint32_t bf_pack(float a, float b) {
   const v2bf h = {(__bf16)a, (__bf16)b};
   return __builtin_bit_cast(uint32_t, h);
 }
-// (a, b) -> NS words of bf16 pairs, high part first (the high part of floats
-// above the largest bf16 is that one, not infinity)
+// (a, b) -> NS words of bf16 pairs, high part first (with two planes, the high
+// part of floats above the largest bf16 is that one, not infinity)
 template <int NS>
 __device__ __forceinline__ void bf_split(float a, float b, uint32_t (&w)[NS]) {
   const float top = __builtin_bit_cast(float, 0x7F7F0000u);
 #pragma unroll
   for (int p = 0; p < NS; ++p) {
-    w[p] = p == 0 ? bf_pack(__builtin_amdgcn_fmed3f(a, -top, top),
-                            __builtin_amdgcn_fmed3f(b, -top, top))
-                  : bf_pack(a, b);
+    w[p] = NS == 2 && p == 0 ? bf_pack(__builtin_amdgcn_fmed3f(a, -top, top),
+                                       __builtin_amdgcn_fmed3f(b, -top, top))
+                             : bf_pack(a, b);
     a -= __builtin_bit_cast(float, w[p] << 16);
     b -= __builtin_bit_cast(float, w[p] & 0xFFFF0000u);
   }
@@ -132,6 +145,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
   constexpr bool AFULL = A_ST % T == 0;
   constexpr int BT = 2 * N;                      // threads that stage B
   constexpr bool CHUNK_SUM = NS == 3;
+  // the row block after which the next chunk goes to LDS.  This and the two
+  // scheduling fences of step are measured (3 x 96^2 x 256 columns, both
+  // directions): without them 7 blocks take 8% longer, 1 and 5 blocks 2 to 4%,
+  // and fences in the others cost up to 7%.
+  constexpr int SWAP = MBW == 7 ? 4 : (MBW - 1) / 2;
   static_assert(BT <= T, "one (half, column) of B per thread");
   extern __shared__ v4u lds[];
   // consecutive logical tiles on one XCD (workgroups go round-robin over 8)
@@ -218,21 +236,20 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
       }
     }
   };
-  // the loaded chunk c to LDS buffer buf; k-steps past the stacked rows
-  // (columns) are zeros, whatever the workspace holds there
-  auto lstore = [&](int c, int buf) {
+  // the loaded chunk c to LDS buffer buf (k-steps past the stacked rows or
+  // columns, up to a chunk's end, are zeros in both operands)
+  auto lstore = [&](int buf) {
     v4u* S = lds + buf * ST;
 #pragma unroll
     for (int j = 0; j < NA; ++j) S[aidx[j]] = ra[j];
     if (stager) {
-      const int64_t k0 = 8 * (int64_t)min(c, c1 - 1) + 4 * bh;
-      const bool tail = 8 * (int64_t)min(c, c1 - 1) + 8 > kext;
       uint32_t wd[4][NS];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float2 v = rb[e];
-        if (tail && k0 + e >= kext) v = make_float2(0.f, 0.f);
-        if (CHUNK_SUM && buf) v = make_float2(-v.x, -v.y);  // odd chunks, see step
+        // odd chunks negated, see step
+        if (CHUNK_SUM && buf) v = make_float2(-v.x, -v.y);
+        if (NS == 3 && !ADJ) v = make_float2(v.x * SPLIT_UP, v.y * SPLIT_UP);
         bf_split<NS>(v.x, v.y, wd[e]);
       }
 #pragma unroll
@@ -277,22 +294,25 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
       for (int j = 0; j < NBW; ++j) {
         if (CHUNK_SUM) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += buf ? -t[j][r] : t[j][r];
+          for (int r = 0; r < 16; ++r)
+            acc[i][j][r] = fmaf(t[j][r], (buf ? -1.f : 1.f) / SPLIT_UP, acc[i][j][r]);
         } else {
           acc[i][j] = t[j];
         }
       }
-      if (i == (MBW - 1) / 2) {
-        lstore(c + 1, buf ^ 1);
+      if (i == SWAP) {
+        if (MBW == 1) __builtin_amdgcn_sched_barrier(0);
+        lstore(buf ^ 1);
         gload(c + 2);
       }
     }
+    if (NBW == 1 && (MBW == 1 || MBW > 3)) __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
   };
 
   if (c0 < c1) {
     gload(c0);
-    lstore(c0, 0);
+    lstore(0);
     gload(c0 + 1);
   }
   __syncthreads();
@@ -306,27 +326,87 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void dtg_split_gemm(SplitGemmParam
   // (Re, Im) of i1 and i1 + 1
   float2* out = P.out + (int64_t)s * P.out_stride + P.ooff[k];
   const int64_t nlim = ADJ ? (int64_t)rk : P.ncols;
-#pragma unroll
-  for (int j = 0; j < NBW; ++j) {
+  const auto store = [&](const v16f& d, int i, int j) {
     const int64_t n = (int64_t)nt * N + (wn * NBW + j) * 32 + ln;
-    if (n >= nlim) continue;
+    if (n >= nlim) return;
     float2* col = out + (int64_t)P.n1 * n;
+    const int blk = mt * MT + wm * MBW + i;
 #pragma unroll
-    for (int i = 0; i < MBW; ++i) {
-      const int blk = mt * MT + wm * MBW + i;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int i1 = blk * 16 + 4 * g + 2 * h;
-        const v16f& d = acc[i][j];
-        if (i1 + 1 < P.n1 && P.vec4) {
-          *(v4f*)(col + i1) = v4f{d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]};
-        } else {
-          if (i1 < P.n1) col[i1] = make_float2(d[4 * g], d[4 * g + 1]);
-          if (i1 + 1 < P.n1) col[i1 + 1] = make_float2(d[4 * g + 2], d[4 * g + 3]);
-        }
+    for (int g = 0; g < 4; ++g) {
+      const int i1 = blk * 16 + 4 * g + 2 * h;
+      const v4f v = {d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]};
+      if (i1 + 1 < P.n1 && P.vec4) {
+        *(v4f*)(col + i1) = v;
+      } else {
+        if (i1 < P.n1) col[i1] = make_float2(v[0], v[1]);
+        if (i1 + 1 < P.n1) col[i1 + 1] = make_float2(v[2], v[3]);
       }
     }
+  };
+  if constexpr (NS == 3) {
+    // of columns that are stored: the others hold what the workspace held
+    bool odd = false;
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) {
+      float z = 0.f;
+#pragma unroll
+      for (int i = 0; i < MBW; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)  // v_maximum3_f32: NaN if any is
+          z = __builtin_elementwise_maximum(
+              __builtin_elementwise_maximum(fabsf(acc[i][j][r]), fabsf(acc[i][j][r + 1])), z);
+      odd = odd || (!(z < __builtin_inff()) &&
+                    (int64_t)nt * N + (wn * NBW + j) * 32 + ln < nlim);
+    }
+    if (__any(odd)) {
+      // block by block, a k-step (stacked row or column, part h) an operand
+#pragma unroll 1
+      for (int b = 0; b < MBW * NBW; ++b) {
+        const int i = b / NBW, j = b % NBW, blk = mt * MT + wm * MBW + i;
+        const int i1 = blk * 16 + (ln >> 1), im = ln & 1;
+        const int64_t n = (int64_t)nt * N + (wn * NBW + j) * 32 + ln;
+        const uint16_t* ap = (const uint16_t*)((const v4u*)P.a + P.aoff[k] + (int64_t)blk * NS * 64);
+        const float* yp = (const float*)(P.y + k * P.nv + i1);
+        const float* bp = (const float*)(P.b + P.boff[k]) + h;
+        v16f sum = v16f{0.f};
+#pragma unroll 1
+        for (int c = c0; c < c1; ++c) {
+          v16f t = v16f{0.f};
+#pragma unroll 1
+          for (int e = 0; e < 8; ++e) {
+            const int64_t kk = 8 * (int64_t)c + e;
+            float av = 0.f, bv = 0.f;
+            if (kk < kext) {
+              if (ADJ) {
+                // rows (i1, Re): Re y, Im y; (i1, Im): Im y, -Re y
+                if (i1 < P.n1) av = yp[2 * kk * P.n1 + (im ^ h)];
+                if (im & h) av = -av;
+                const int64_t row = min(n, (int64_t)rpad - 1);
+                bv = bp[2 * ((((kk >> DTG_LW_A) * rpad + row) << DTG_LW_A) +
+                             (kk & ((1 << DTG_LW_A) - 1)))];
+              } else {
+                const uint16_t* a8 = ap + (int64_t)c * astep * 8 +
+                                     (32 * (e >> 2) + ln) * 8 + 2 * (e & 3) + h;
+#pragma unroll
+                for (int p = NS - 1; p >= 0; --p)
+                  av += __builtin_bit_cast(float, (uint32_t)a8[p * 64 * 8] << 16);
+                bv = bp[2 * ((((n >> DTG_LW_F) * rpad + kk) << DTG_LW_F) +
+                             (n & ((1 << DTG_LW_F) - 1)))];
+              }
+            }
+            t = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, t, 0, 0, 0);
+          }
+          sum += t;
+        }
+        store(sum, i, j);
+      }
+      return;
+    }
   }
+#pragma unroll
+  for (int j = 0; j < NBW; ++j)
+#pragma unroll
+    for (int i = 0; i < MBW; ++i) store(acc[i][j], i, j);
 }
 
 // waves: even row-block counts as 2 x WN of MT/2 x 2 blocks (less LDS traffic

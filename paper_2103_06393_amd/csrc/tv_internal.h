@@ -131,6 +131,7 @@ struct tv_plan_s {
   int64_t dtg_rows = 0;            // sum of dtg_rpad
   uint4* d_abf = nullptr;          // stacked U1 split into bf16 planes, 8-row chunks
   int32_t* d_drow = nullptr;       // first stacked row of each tensor in A_k, [k][j]
+  float2* d_scale = nullptr;       // powers of two of each tensor in the GEMMs, [j][k]
   std::vector<int64_t> dtg_abfoff; // uint4 offset of component k in d_abf
   bool with_dtg = true;             // pack the GEMM operands (FP32 plans)
   bool dtg_packed = false;          // the GEMM operands are part of the plan
@@ -197,6 +198,7 @@ tv_status set_split(tv_plan_s* p, int op, int S);
 // decompress-then-GEMM forward (tv_dtg.hip)
 tv_status dtg_layout(tv_plan_s* p, const std::vector<TensorMeta>& meta);
 void dtg_default(tv_plan_s* p);  // the path and launch configuration of a new plan
+tv_status launch_dtg_scale(const tv_plan_s* p, int64_t j0, hipStream_t st);  // set-up: d_scale from column j0 on
 tv_status launch_dtg_pack(const tv_plan_s* p, hipStream_t st);  // set-up: A_k from the bound U1
 bool dtg_supported(const tv_plan_s* p);
 // 32-row blocks of one decompress-then-GEMM workgroup tile (tv_dtg.hip), of
