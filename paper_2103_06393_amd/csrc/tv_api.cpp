@@ -862,13 +862,21 @@ tv_status grow_plan_append(tv_plan p, const int32_t* ranks, const double* cores,
     // split at least 4 k-steps), at most 16 ways (the reduction, one
     // workgroup per column of U, reads every split's partials: at 64 splits
     // it took longer than the GEMM), fewer where the workspace would not hold
-    // their partials
+    // their partials, and slabs half as high with half the splits each, again
+    // and again, where it would not hold one of all i3
     const int64_t tiles = std::max<int64_t>(1, dtg_colgemm_tiles(p, p->dtg_nbw_a));
     const int64_t nst = ((int64_t)g.n2 * g.n3 + kDtgRowPad - 1) / kDtgRowPad;
-    int S = (int)std::max<int64_t>(
+    const int S = (int)std::max<int64_t>(
         1, std::min<int64_t>({(1024 + tiles - 1) / tiles, 16, nst / 4}));
+    const auto fits = [&] { return dtg_workspace_bytes(p, 1) <= p->grow_adj_ws; };
+    p->dtg_s3_a = g.n3;
     p->dtg_split_a = S;
-    while (S > 1 && dtg_workspace_bytes(p, 1) > p->grow_adj_ws) p->dtg_split_a = S /= 2;
+    while (p->dtg_split_a > 1 && !fits()) p->dtg_split_a /= 2;
+    if (!fits()) p->dtg_split_a = S;
+    while (p->dtg_s3_a > 1 && !fits()) {
+      p->dtg_s3_a = (p->dtg_s3_a + 1) / 2;
+      p->dtg_split_a = std::max(1, p->dtg_split_a / 2);
+    }
   }
   p->use_dtg[1] = p->dtg_packed && g.m >= kGrowColGemmMin &&
                   dtg_workspace_bytes(p, 1) <= p->grow_adj_ws;
