@@ -73,7 +73,7 @@ typedef TV_ENUM(tv_status_e) {
  * and form the six products of weight 2^-16 and above on BF16 MFMA, summed in
  * FP32 (where those are not finite, FP32 MFMA forms them from the operands).
  * All 24 bits count for every FP32 vector entry, and for factor entries down
- * to 2^-100 of the largest of their tensor's factor.  BF16X3: every FP32
+ * to 2^-70 of the largest of their tensor's factor.  BF16X3: every FP32
  * operand x is split into bf16 hi = rn(x), lo = rn(x - hi) and a*b is formed as
  * hi*hi + hi*lo + lo*hi on BF16 MFMA with FP32 accumulation. */
 typedef TV_ENUM(tv_precision_e) { TV_PREC_FP32 = 0, TV_PREC_BF16X3 = 1 } tv_precision;

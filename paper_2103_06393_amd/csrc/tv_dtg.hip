@@ -47,12 +47,13 @@ __device__ __forceinline__ float pow2_inv(float v) {
   return __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, v));
 }
 
-// The powers of two that bring a tensor's operands of the GEMMs near 1, from
-// the largest real or imaginary parts of its factors, at plan set-up, a wave a
-// factor: scale[k + q j] = (of modes 2 and 3, 1 / of U1).  The adjoint's B is
-// decompressed with the first and the final sum takes it back; U1 is packed
-// divided by the second, and the forward's B decompressed with it (1 unless U1
-// is below 2^-10, which orthonormal columns are not).
+// The powers of two that bring a tensor's operands of the GEMMs up to 2^-40
+// where they are smaller (above that a bf16's range holds the three planes of
+// entries down to 2^-70 of the largest), from the largest real or imaginary
+// parts of its factors, at plan set-up, a wave a factor: scale[k + q j] = (of
+// modes 2 and 3, 1 / of U1).  The adjoint's B is decompressed with the first
+// and the final sum takes it back; U1 is packed divided by the second, and the
+// forward's B decompressed with it.
 __global__ __launch_bounds__(256) void dtg_scale_kernel(const TensorMeta* meta, const float2* cores,
                                                         const float2* u1t, const float2* u2t,
                                                         const float2* u3t, float2* scale, int q,
@@ -76,10 +77,11 @@ __global__ __launch_bounds__(256) void dtg_scale_kernel(const TensorMeta* meta, 
   if (lane == 0) ex[wave] = top ? (top >> 23) - 127 : 0;
   __syncthreads();
   if (threadIdx.x) return;
-  const auto pow2 = [](int e) {
-    return __builtin_bit_cast(float, (127 + min(max(e, -100), 100)) << 23);
-  };
-  scale[k + q * j] = make_float2(pow2(-ex[0] - ex[2] - ex[3]), pow2(ex[1] < -10 ? ex[1] : 0));
+  // 2^-e of an exponent below -40
+  const auto up = [](int e) { return min(max(-40 - e, 0), 100); };
+  scale[k + q * j] =
+      make_float2(__builtin_bit_cast(float, (127 + up(ex[0] + ex[2] + ex[3])) << 23),
+                  __builtin_bit_cast(float, (127 - up(ex[1])) << 23));
 }
 
 // B rows of one tensor for cnt <= t3w values of i3, two small products:

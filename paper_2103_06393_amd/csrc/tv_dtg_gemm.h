@@ -21,7 +21,7 @@
 //     negated products and are subtracted, which cancels it (adjoint of 512
 //     dipole columns on 128^3, random y: error 3.2e-6 without, 4.9e-7 with).
 //     The low plane runs out of exponent below 2^-110: the plan's operand (U1;
-//     the adjoint's B) is brought near 1, each tensor by itself, and what a
+//     the adjoint's B) is brought up to 2^-40, each tensor by itself, and what a
 //     call brings (y; B with x in it) is split as 2^17 times itself, which the
 //     running sum takes back as it adds a chunk.  A wave whose sums are not
 //     finite (an infinity or NaN among its operands, or products from about
