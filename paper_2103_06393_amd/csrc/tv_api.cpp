@@ -303,15 +303,28 @@ static void pack_apack_bf(const tv_grid& g, int r1, const double* u1, int nbt, u
 
 // The fused kernels' tile of a new plan, instead of the one covering the
 // fewest columns: the warp-specialised kernels need t2 to be a multiple of 32
-// and run 2 to 4 times faster per covered column than the phased ones, whose
-// mode 3 grows with t3 (adjoint per covered column, us: 81x44x108 x 250, ranks
-// 15 to 18, t2 = 32 1650, 16 3140, 4 7200; 21x33x27 x 37, ranks 4 to 12, t2 =
-// 64 18, 8 23, 4 46; 24x10x90 x 100, ranks 4 to 8, t2 = 32 22, 8 46, 4 43).
+// and mostly take less time per covered column than the phased ones, whose
+// mode 3 grows with t3.  How much less was measured on 210 plans of 16 to 160
+// voxels a side, every tile: forward, and adjoint in FP32 up to 128 voxel rows,
+// 1.2 to 1.6 times at t2 >= 8 and up to 4 at t2 = 2, more the larger the plan;
+// over 128 rows 0.75 to 1 (3 x 148x23x49 x 15: 64% of the time at t2 = 8); in
+// BF16X3, whose phased adjoint gains more from the faster mode 1, 0.85 to 1.5
+// (3 x 90x37x40 x 43: 65% at t2 = 8).  Against the fewest columns the adjoint
+// chosen so takes 0.86 (FP32) and 0.96 (BF16X3) of the time in the mean, and a
+// fifth more at most where it loses.  Columns that an idle chip takes in the
+// same time are not counted in BF16X3's adjoint.
 // The adjoint's keeps within the static scratch what was within it.
 static tv_status default_tile(tv_plan_s* p, int op) {
   Tiling& cur = op == 0 ? p->tiling : p->tiling_a;
   const int64_t mean_core = p->g_off.back() / ((int64_t)p->grid.q * p->grid.m);
   const size_t ws0 = fused_adjoint_ws(p);
+  const bool fp32 = p->precision == TV_PREC_FP32;
+  // per covered column, phased against warp-specialised: t2 >= 8, 4 (small and
+  // large cores), 2
+  static constexpr double kMost[] = {2.0, 2.0, 3.0, 4.0}, kTall[] = {1.0, 1.0, 1.0, 1.5},
+                          kSplit[] = {1.5, 1.4, 1.8, 2.0}, kSplitTall[] = {1.1, 1.1, 1.5, 2.0};
+  const int n1 = p->grid.n1;
+  const double* w = op == 0 || (fp32 && n1 <= 128) ? kMost : fp32 ? kTall : n1 <= 64 ? kSplit : kSplitTall;
   Tiling best = cur;
   double cost = -1.0;
   for (int t2 = cur.nwg; t2 >= 2; t2 /= 2) {
@@ -324,10 +337,15 @@ static tv_status default_tile(tv_plan_s* p, int op) {
       if (ws > ws0 && ws > TV_STATIC_SCRATCH_BYTES) continue;
     }
     const double per = ws_supported(p, T, op == 1) ? 1.0
-                       : t2 >= 8                   ? 2.0
-                       : t2 == 4                   ? (mean_core <= 300 ? 2.0 : 3.0)
-                                                   : 4.0;
-    const double c = per * (double)T.tiles * T.t2 * T.t3;
+                       : t2 >= 8                   ? w[0]
+                       : t2 == 4                   ? (mean_core <= 300 ? w[1] : w[2])
+                                                   : w[3];
+    double c = per * (double)T.tiles * T.t2 * T.t3;
+    if (op == 1 && !fp32) {
+      const int64_t base = p->grid.q * T.tiles;
+      const int64_t splits = std::min<int64_t>({64, (1024 + base - 1) / base, p->grid.m});
+      c *= std::max(1.0, 512.0 / (double)(base * splits));
+    }
     if (cost < 0.0 || c < cost) {
       cost = c;
       best = T;
