@@ -189,7 +189,7 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
 /* Launch configuration of one direction of a plan's products (what the
  * autotuner chooses; set-up call, not thread-safe against concurrent
  * products on the same plan).  A new plan starts on the path that a rule on
- * its size picks, in a workspace of at most 4 GiB: path 1 from 0.3 GFLOP of
+ * its size picks, in a workspace of at most 6 GiB: path 1 from 0.3 GFLOP of
  * mode 1 (8 n1 n2 n3 sum r1) forward, and 0.4 adjoint, or 1.2 below 256 stacked
  * rows per component (for tv_rmatvec only where tv_rmatvec_noalloc can run it
  * too; tv_aca_rmatvec goes by the size alone).

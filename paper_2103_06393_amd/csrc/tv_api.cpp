@@ -304,15 +304,17 @@ static void pack_apack_bf(const tv_grid& g, int r1, const double* u1, int nbt, u
 // The fused kernels' tile of a new plan, instead of the one covering the
 // fewest columns: the warp-specialised kernels need t2 to be a multiple of 32
 // and mostly take less time per covered column than the phased ones, whose
-// mode 3 grows with t3.  How much less was measured on 210 plans of 16 to 160
-// voxels a side, every tile: forward, and adjoint in FP32 up to 128 voxel rows,
-// 1.2 to 1.6 times at t2 >= 8 and up to 4 at t2 = 2, more the larger the plan;
-// over 128 rows 0.75 to 1 (3 x 148x23x49 x 15: 64% of the time at t2 = 8); in
-// BF16X3, whose phased adjoint gains more from the faster mode 1, 0.85 to 1.5
-// (3 x 90x37x40 x 43: 65% at t2 = 8).  Against the fewest columns the adjoint
-// chosen so takes 0.86 (FP32) and 0.96 (BF16X3) of the time in the mean, and a
-// fifth more at most where it loses.  Columns that an idle chip takes in the
-// same time are not counted in BF16X3's adjoint.
+// mode 3 grows with t3.  How much less was measured on 280 plans of 16 to 250
+// voxels a side, every tile: forward, and adjoint in FP32, 1.2 to 1.8 times at
+// t2 >= 8 and up to 4 at t2 = 2, more the larger the plan; FP32 adjoint of 9 to
+// 12 blocks of 16 voxel rows, three a wave, 0.75 to 1.2 (3 x 148x23x49 x 15: 64%
+// of the time at t2 = 8; 13 blocks and more 1.5 to 1.8 again: 3 x 236x106x109 x
+// 139, 3.4 ms at t2 = 8, 2.5 at 32); BF16X3, whose phased adjoint gains more
+// from the faster mode 1, 0.85 to 1.5 (3 x 90x37x40 x 43: 65% at t2 = 8).
+// Against the fewest columns the adjoint chosen so takes 0.86 (FP32) and 0.96
+// (BF16X3) of the time in the mean, and a quarter more at most where it loses.
+// Columns that an idle chip takes in the same time are not counted in BF16X3's
+// adjoint.
 // The adjoint's keeps within the static scratch what was within it.
 static tv_status default_tile(tv_plan_s* p, int op) {
   Tiling& cur = op == 0 ? p->tiling : p->tiling_a;
@@ -323,8 +325,9 @@ static tv_status default_tile(tv_plan_s* p, int op) {
   // large cores), 2
   static constexpr double kMost[] = {2.0, 2.0, 3.0, 4.0}, kTall[] = {1.0, 1.0, 1.0, 1.5},
                           kSplit[] = {1.5, 1.4, 1.8, 2.0}, kSplitTall[] = {1.1, 1.1, 1.5, 2.0};
-  const int n1 = p->grid.n1;
-  const double* w = op == 0 || (fp32 && n1 <= 128) ? kMost : fp32 ? kTall : n1 <= 64 ? kSplit : kSplitTall;
+  const int nb = (p->grid.n1 + 15) / 16;
+  const bool tall = fp32 ? nb > 8 && nb <= 12 : nb > 4;
+  const double* w = op == 0 ? kMost : fp32 ? (tall ? kTall : kMost) : tall ? kSplitTall : kSplit;
   Tiling best = cur;
   double cost = -1.0;
   for (int t2 = cur.nwg; t2 >= 2; t2 /= 2) {

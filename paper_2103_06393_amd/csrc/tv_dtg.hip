@@ -593,16 +593,20 @@ bool dtg_supported(const tv_plan_s* p) { return p->dtg_packed && p->grid.q <= DT
 // 163).  Adjoint tiles of 256 stacked rows, or 128 where those pad a seventh
 // less or the rows fit one (two workgroups then share a CU), column splits
 // towards a full chip, 48 columns each at least, 32 at most.
-// FP32 plans' adjoint: FP32 chains of at most 256 columns (512 where all
-// partials of Z would pass 2 GiB at that), since the fused adjoint sums little
-// in FP32 before its FP64 sum (81x44x108 x 250: error against 64 bits 2.7e-7
-// there, 2.4e-7 with chains of 256 columns, which take 2.57 ms, 2.95 with 128).
-// Slabs as high as that leaves 64 splits and the whole workspace 4 GiB; a plan
-// whose single i3 needs more stays on the fused kernels.
+// FP32 plans' adjoint: FP32 chains of 256 columns (512 where all partials of Z
+// would pass 2 GiB at that), since the fused adjoint sums little in FP32 before
+// its FP64 sum (81x44x108 x 250: error against 64 bits 2.7e-7 there, 2.4e-7
+// with chains of 256 columns, which take 2.57 ms, 2.95 with 128); up to 1024
+// columns where 64 splits of a slab leave no shorter ones (256^3 x 40, two
+// seeds: 2.3 and 2.4e-7 in 1.45 ms; 1.9 and 2.0e-7 in 1.79 with slabs for chains
+// of 256; fused 2.3 and 3.0e-7 in 3.6).
+// Slabs as high as that and a workspace of 6 GiB in all allow (at 4 GiB 256^3 x
+// 512 takes 2% longer, in BF16X3 x 256 6%); a plan whose single i3 needs more
+// stays on the fused kernels.
 void dtg_default(tv_plan_s* p) {
   if (!dtg_supported(p)) return;
   const tv_grid& g = p->grid;
-  constexpr size_t bound = (size_t)4 << 30;
+  constexpr size_t bound = (size_t)6 << 30;
   const double gflop = 8e-9 * (double)p->sum_r1 * g.n1 * g.n2 * g.n3;
   const int64_t rows_k = p->dtg_rows / g.q;
   const auto pow2 = [](int64_t n, int64_t most) {
@@ -629,7 +633,7 @@ void dtg_default(tv_plan_s* p) {
     if (dtg_planes(p) == 3) {
       const int64_t chain = z * nslab * ((cols + 255) / 256) <= (int64_t)2 << 30 ? 256 : 512;
       split = std::max(split, (cols + chain - 1) / chain);
-      if (split > 64 && p->dtg_s3_a > 1) continue;
+      if (cols > 64 * 1024 && p->dtg_s3_a > 1) continue;
     }
     p->dtg_split_a = (int)std::min<int64_t>(split, 64);
     fits[1] = dtg_workspace_bytes(p, 1) <= bound;
