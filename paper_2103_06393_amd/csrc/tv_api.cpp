@@ -324,10 +324,11 @@ static tv_status default_tile(tv_plan_s* p, int op) {
   // per covered column, phased against warp-specialised: t2 >= 8, 4 (small and
   // large cores), 2
   static constexpr double kMost[] = {2.0, 2.0, 3.0, 4.0}, kTall[] = {1.0, 1.0, 1.0, 1.5},
-                          kSplit[] = {1.5, 1.4, 1.8, 2.0}, kSplitTall[] = {1.1, 1.1, 1.5, 2.0};
+                          kSplit[] = {1.5, 1.4, 1.8, 2.0}, kSplitTall[] = {1.08, 1.08, 2.0, 1.2};
   const int nb = (p->grid.n1 + 15) / 16;
   const bool tall = fp32 ? nb > 8 && nb <= 12 : nb > 4;
   const double* w = op == 0 ? kMost : fp32 ? (tall ? kTall : kMost) : tall ? kSplitTall : kSplit;
+  const int64_t small = w == kSplitTall ? 1000 : 300;
   Tiling best = cur;
   double cost = -1.0;
   for (int t2 = cur.nwg; t2 >= 2; t2 /= 2) {
@@ -341,7 +342,7 @@ static tv_status default_tile(tv_plan_s* p, int op) {
     }
     const double per = ws_supported(p, T, op == 1) ? 1.0
                        : t2 >= 8                   ? w[0]
-                       : t2 == 4                   ? (mean_core <= 300 ? w[1] : w[2])
+                       : t2 == 4                   ? (mean_core <= small ? w[1] : w[2])
                                                    : w[3];
     double c = per * (double)T.tiles * T.t2 * T.t3;
     if (op == 1 && !fp32) {
