@@ -109,7 +109,7 @@ typedef struct {
    * (0: phased, 1: warp-specialised producer/consumer, 2: decompress-then-
    * GEMM, for which tile_t2 is the i3 values per slab, tile_t3 the GEMM's
    * tile width in units of 64 columns (adjoint: stacked rows) and splits its
-   * k-step (adjoint: column) split count)                                         */
+   * k-step (adjoint: column) split count)                                  */
   int32_t tile_t2[2], tile_t3[2], splits[2], kernel[2];
 } tv_plan_info_t;
 
@@ -198,7 +198,7 @@ tv_status tv_rmatvec(tv_plan plan, const void* y, int64_t ldy, int32_t nrhs,
  *     covering the fewest columns), splits = column-range splits (split-K
  *     over j), row_cap = row blocks per consumer wave (forward 8; adjoint 2
  *     or 3).
- *   path 1 (FP32 plans): decompress-then-GEMM: per slab of slab_i3 values
+ *   path 1: decompress-then-GEMM: per slab of slab_i3 values
  *     of i3 (0: all), modes 3 and 2 of every tensor are decompressed into
  *     the stacked operand B_k = [x_1 M_1; ...] (unscaled for the adjoint) in
  *     the workspace, then the forward runs Y^k_(1) = A_k B_k as one MFMA

@@ -46,13 +46,15 @@
 // per lane: two waves per SIMD hide each other's LDS reads and barriers.
 //
 // Bound by the matrix cores and their power: torch's bf16 product reaches
-// 1378 TFLOP/s on this card (230 after the six products).  Measured, against
+// 1378 TFLOP/s on this card (230 after the six products); counters at 256^3 x
+// 2048: matrix cores 68 % (forward) and 65 % busy at 1.73 to 1.75 GHz, waves 23 %
+// of their time waiting, 15.8 and 16.9 GB fetched for a slab of 13.1.  Against
 // the FP32 MFMA GEMM (v_mfma_f32_32x32x2f32, 1/16 of the bf16 rate) that this
-// one replaced: 256^3 x 2048 columns, adjoint GEMM 56.4 -> 35.2 ms (203
+// one replaced: 256^3 x 2048 columns, adjoint GEMM 56.4 -> 34.8 ms (205
 // TFLOP/s; 31.2 ms without CHUNK_SUM), relative error against 64 bits 1.2e-6
-// -> 4.4e-7 (1.5e-6 without CHUNK_SUM, 7.7e-7 without the negated chunks); 205 x 109 x 270 x 287
-// forward GEMM 7.5 -> 4.3 ms, error 1.8e-6 -> 4.9e-7; BF16X3 256^3 x 256
-// forward 3.0 -> 2.3, adjoint 3.1 -> 2.4 ms.
+// -> 4.4e-7 (1.5e-6 without CHUNK_SUM, 7.7e-7 without the negated chunks);
+// 205 x 109 x 270 x 287 forward GEMM 7.5 -> 4.4 ms, error 1.8e-6 -> 4.9e-7;
+// BF16X3 256^3 x 256 forward 3.0 -> 2.6, adjoint 3.1 -> 2.8 ms.
 #pragma once
 
 #include "tv_internal.h"
